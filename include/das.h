@@ -151,7 +151,9 @@ typedef struct das_batch {
 /* Kernel family and schedule selection (measurement and tests). */
 typedef enum das_attn_path {
   DAS_PATH_AUTO = 0,     /* library choice                                   */
-  DAS_PATH_VALU = 1,     /* vector-ALU kernel (the only path for fp32)       */
+  DAS_PATH_VALU = 1,     /* vector-ALU kernel (on fp32 caches the only path that
+                            can be asked for; DAS_PATH_AUTO runs most fp32
+                            requests on the matrix cores, in full fp32)      */
   DAS_PATH_MFMA = 2,     /* matrix-core kernel over prefix splits (bf16)     */
   DAS_PATH_BALANCED = 3  /* matrix-core kernel, persistent balanced schedule:
                             every resident wave streams an equal share of
@@ -178,8 +180,9 @@ typedef struct das_attn_options {
 
 /*
  * Bytes of device workspace an attention call with these shapes needs (the
- * partial results of the prefix splits or pieces: fp16 records with fp32
- * maxima and sums on the matrix-core paths, fp32 on the vector-ALU path).
+ * partial results of the prefix splits or pieces: records of fp16 (bf16
+ * caches) or fp32 outputs with fp32 maxima and sums on the matrix-core paths,
+ * fp32 arrays on the vector-ALU path).
  * Returns 0 for arguments that the attention entry points would reject.
  * `opts` may be NULL.
  */

@@ -83,13 +83,14 @@ struct TileMap {
   long long workers;  // W (wave-uniform)
 };
 
+template <int TT>
 __device__ __forceinline__ TileMap tile_map(const AttnParams &p, int lane, bool report) {
   TileMap m;
   const int s_raw = lane < p.batch ? p.prefix_len[lane] : 0;
   bool bad;
   m.s = clamp_prefix(s_raw, p.max_pages, &bad);
   if (report && bad && lane < p.batch) report_error(p.dev_error, DAS_DEVERR_PREFIX);
-  m.tu = 2 * ((m.s + kPage - 1) / kPage) + ((p.w + 31) >> 5);
+  m.tu = kPage / TT * ((m.s + kPage - 1) / kPage) + (p.w + TT - 1) / TT;
   const long long own = lane < p.batch ? static_cast<long long>(m.tu) * p.hkv : 0;
   m.incl = wave_incl_scan(own, lane);
   m.total = readlane64(m.incl, 63);
@@ -126,19 +127,24 @@ __device__ __forceinline__ Cursor uniform(const Cursor &x) {
   return y;
 }
 
-template <int DH, int NQ>
+template <typename T, int DH, int NQ>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_balanced_kernel(AttnParams p) {
-  using G = Geo<DH, NQ, 2>;
+  using G = Geo<T, DH, NQ, 2>;
+  constexpr int ES = G::ES;
+  constexpr int TT = G::TT;
+  constexpr int TPP = G::TPP;
+  constexpr int QK = G::QK;
   constexpr int KS = G::KS;
   constexpr int DT = G::DT;
   __shared__ __attribute__((aligned(16))) uint8_t ring[2 * G::SLOT];
   // the record of a piece that ends in the middle of the range (only the
   // range's first unit can), written to global memory with the range's last
   // flush
-  constexpr int kStash = static_cast<int>(piece_record_bytes(balanced_max_rows(DH), DH));
+  constexpr int kStash =
+      static_cast<int>(piece_record_bytes(balanced_stash_rows(16 * NQ, DH, ES), DH, ES));
   __shared__ __attribute__((aligned(16))) uint8_t stash[kStash];
-  static_assert(2 * G::SLOT + kStash == balanced_lds_per_worker(DH),
+  static_assert(2 * G::SLOT + kStash == balanced_lds_per_worker(16 * NQ, DH, ES),
                 "the host's worker count assumes this LDS per worker");
 
   const int lane = threadIdx.x;
@@ -146,11 +152,11 @@ void attn_balanced_kernel(AttnParams p) {
   const int lg = lane >> 4;
   const int j = blockIdx.x;
 
-  const TileMap tm = tile_map(p, lane, j == 0);
+  const TileMap tm = tile_map<TT>(p, lane, j == 0);
   if (j >= tm.workers) return;
-  const long long T = tm.total, W = tm.workers;
-  const long long g0 = T * j / W;
-  const long long n = T * (j + 1) / W - g0;  // >= 1: W <= max(1, T / 16)
+  const long long tiles = tm.total, W = tm.workers;
+  const long long g0 = tiles * j / W;
+  const long long n = tiles * (j + 1) / W - g0;  // >= 1: W <= max(1, tiles / 16)
 
   // the unit holding g0: sequences ending at or before g0 come first
   const uint64_t done = __builtin_amdgcn_ballot_w64(lane < p.batch && tm.incl <= g0);
@@ -168,49 +174,44 @@ void attn_balanced_kernel(AttnParams p) {
   }
   const char *kl = static_cast<const char *>(p.k_layer);
   const char *vl = static_cast<const char *>(p.v_layer);
-  const size_t tok_bytes = static_cast<size_t>(p.hkv) * DH * 2;  // block row stride
-  // per-lane byte offsets of a fragment inside a page half (as in the
-  // split-grid kernel): key token slot 8(n/4) + n%4, column 8g; value token
-  // group g, head dim n
-  const uint32_t lane_k = ((8 * (ln >> 2) + (ln & 3)) * DH + 8 * lg) * 2;
-  const uint32_t lane_v = (lg * DH + ln) * 16;
+  const size_t tok_bytes = static_cast<size_t>(p.hkv) * DH * ES;  // block row stride
+  // per-lane byte offsets of a fragment inside a tile's keys and values (as
+  // in the split-grid kernel)
+  const uint32_t lane_k = G::key_lane(ln, lg);
+  const uint32_t lane_v = G::val_lane(ln, lg);
 
-  // Q fragments of a unit (B operand of S^T = K Q^T: lane holds dims
-  // 8g..8g+7 of row n); rows past the block's last are clamped and never
+  // Q fragments of a unit (B operand of S^T = K Q^T: lane holds 16 bytes of
+  // row n per fragment); rows past the block's last are clamped and never
   // written
   auto q_row = [&](const Cursor &x, int qt) {
     const int row = min(qt * 16 + ln, p.rows - 1);
     const int i = row / p.group, g = row % p.group;
-    return static_cast<const bf16_t *>(p.q) +
+    return static_cast<const T *>(p.q) +
            ((static_cast<size_t>(x.b) * p.w + i) * p.hq + x.kvh * p.group + g) * DH;
   };
-  auto load_q = [&](const Cursor &x, u32x4 (&qf)[NQ][KS]) {
+  auto load_q = [&](const Cursor &x, u32x4 (&qf)[NQ][QK]) {
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) {
-      const int row = min(qt * 16 + ln, p.rows - 1);
-      const int i = row / p.group, g = row % p.group;
-      const bf16_t *qrow = static_cast<const bf16_t *>(p.q) +
-                           ((static_cast<size_t>(x.b) * p.w + i) * p.hq + x.kvh * p.group + g) * DH;
+      const T *qrow = q_row(x, qt);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        qf[qt][ks] = *reinterpret_cast<const u32x4 *>(qrow + 32 * ks + 8 * lg);
+      for (int ks = 0; ks < QK; ++ks)
+        qf[qt][ks] = *reinterpret_cast<const u32x4 *>(qrow + (64 * ks + 16 * lg) / ES);
     }
   };
-  // Sources of a tile: a prefix tile's 32-token key half and value half of
-  // its page; an out-of-range page id is reported and read as page 0 (the
+  // Sources of a tile: a prefix tile's keys and values in its page; an out-of-range page id is reported and read as page 0 (the
   // tile is then masked out).
   auto tile_src = [&](const Cursor &x, int page, const char *&kbase, const char *&vbase,
                       bool &ok) {
     kbase = kl;
     vbase = vl;
     ok = true;
-    if (x.t >= 2 * x.np) return;
+    if (x.t >= TPP * x.np) return;
     ok = page >= 0 && page < p.num_pages;
     if (!ok) report_error(p.dev_error, DAS_DEVERR_PAGE);
     const size_t off = (static_cast<size_t>(x.kvh) * p.num_pages + (ok ? page : 0)) *
-                       kPage * DH * 2;
-    const int u = x.t & 1;
-    kbase = kl + off + (32 * u) * DH * 2;
+                       kPage * DH * ES;
+    const int u = x.t % TPP;
+    kbase = kl + off + 64 * DH * u;
     vbase = vl + off + 64 * DH * u;
   };
   // Loads of a tile into ring slot `si`, in three parts (key fragments of
@@ -219,36 +220,36 @@ void attn_balanced_kernel(AttnParams p) {
   auto issue_part = [&](int si, const Cursor &x, int part, const char *kbase,
                         const char *vbase) {
     uint8_t *slot = ring + si * G::SLOT;
-    if (x.t < 2 * x.np) {
+    if (x.t < TPP * x.np) {
       if (part < 2) {
         const auto r = buffer_of(uniform_ptr(kbase), 64 * DH);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          dma16(r, lane_k, (4 * part * DH + 32 * ks) * 2, slot + (part * KS + ks) * kFragBytes);
+          dma16(r, lane_k, G::key_frag(part * KS + ks), slot + (part * KS + ks) * kFragBytes);
       } else {
         const auto r = buffer_of(uniform_ptr(vbase), 64 * DH);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-          dma16(r, lane_v, 256 * dt, slot + (2 * KS + dt) * kFragBytes);
+          dma16(r, lane_v, G::val_frag(dt), slot + (2 * KS + dt) * kFragBytes);
       }
     } else {
       // draft block tile u: key fragments by token slot, value rows raw
-      const int u = x.t - 2 * x.np;
+      const int u = x.t - TPP * x.np;
       const size_t row0 = static_cast<size_t>(x.b) * p.w * p.hkv + x.kvh;
-      const char *kblk = static_cast<const char *>(p.kb) + row0 * DH * 2;
-      const char *vblk = static_cast<const char *>(p.vb) + row0 * DH * 2;
+      const char *kblk = static_cast<const char *>(p.kb) + row0 * DH * ES;
+      const char *vblk = static_cast<const char *>(p.vb) + row0 * DH * ES;
       if (part < 2) {
-        const int tok = min(32 * u + 8 * (ln >> 2) + 4 * part + (ln & 3), p.w - 1);
+        const int tok = min(TT * u + G::key_token(ln, part * KS), p.w - 1);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          dma16(kblk + tok * tok_bytes + (32 * ks + 8 * lg) * 2,
+          dma16(kblk + tok * tok_bytes + G::key_col(part * KS + ks, lg),
                 slot + (part * KS + ks) * kFragBytes);
       } else {
 #pragma unroll
         for (int f = 0; f < DT; ++f) {
-          const int o = f * kFragBytes + 16 * lane;  // byte in the [32][DH] half
-          const int tok = min(32 * u + o / (2 * DH), p.w - 1);
-          dma16(vblk + tok * tok_bytes + o % (2 * DH), slot + (2 * KS + f) * kFragBytes);
+          const int o = f * kFragBytes + 16 * lane;  // byte in the [TT][DH] rows
+          const int tok = min(TT * u + o / (ES * DH), p.w - 1);
+          dma16(vblk + tok * tok_bytes + o % (ES * DH), slot + (2 * KS + f) * kFragBytes);
         }
       }
     }
@@ -275,27 +276,19 @@ void attn_balanced_kernel(AttnParams p) {
       if (whole) {
         const float inv = 1.f / st.l[qt];
         const int i = row / p.group, h = x.kvh * p.group + row % p.group;
-        bf16_t *orow = static_cast<bf16_t *>(p.out) +
-                       ((static_cast<size_t>(x.b) * p.w + i) * p.hq + h) * DH;
+        T *orow = static_cast<T *>(p.out) +
+                  ((static_cast<size_t>(x.b) * p.w + i) * p.hq + h) * DH;
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          const f32x4 o = st.o[qt][dt];
-          u32x2 packed;
-          packed[0] = static_cast<uint32_t>(f32_to_bf16(o[0] * inv)) |
-                      (static_cast<uint32_t>(f32_to_bf16(o[1] * inv)) << 16);
-          packed[1] = static_cast<uint32_t>(f32_to_bf16(o[2] * inv)) |
-                      (static_cast<uint32_t>(f32_to_bf16(o[3] * inv)) << 16);
-          *reinterpret_cast<u32x2 *>(orow + 16 * dt + 4 * lg) = packed;
-        }
+        for (int dt = 0; dt < DT; ++dt) store_out4(orow + 16 * dt + 4 * lg, st.o[qt][dt] * inv);
         if (lg == 0 && p.lse)
           p.lse[(static_cast<size_t>(x.b) * p.hq + h) * p.w + i] =
               (st.m[qt] + log2f(st.l[qt])) * 0.69314718055994530942f;
       } else {
         // a piece record of its own (256-byte aligned, so its lines are
-        // written by this wave alone), in half the bytes of fp32 partials:
-        // the stores of a piece written in the middle of a worker's range
+        // written by this wave alone), for bf16 in half the bytes of fp32
+        // partials: the stores of a piece written in the middle of a worker's range
         // delay its next tile waits
-        write_piece_row<DH>(rec, p.rows, row, lg, st.o[qt], st.m[qt], st.l[qt]);
+        write_piece_row<T, DH>(rec, p.rows, row, lg, st.o[qt], st.m[qt], st.l[qt]);
       }
     }
   };
@@ -331,7 +324,7 @@ void attn_balanced_kernel(AttnParams p) {
   // loaded one window or one unit ahead; the wait at the top of every tile
   // completes them with the tile.
   Cursor cu = c0;
-  int pw0 = (c0.t >> 1) & ~63;
+  int pw0 = (c0.t / TPP) & ~63;
   int pwin = load_window(cu.b, pw0);
   int x_pw0 = -1;  // first page of the prefetched next window (-1: none)
   int pwin_x = 0;
@@ -343,13 +336,13 @@ void attn_balanced_kernel(AttnParams p) {
   // start of the current unit (qn); with two there is no room for a second
   // set, and they are loaded when the unit starts (one round trip per unit).
   constexpr bool kPrefetchQ = NQ == 1;
-  u32x4 qf[NQ][KS], qn[kPrefetchQ ? NQ : 1][KS];
+  u32x4 qf[NQ][QK], qn[kPrefetchQ ? NQ : 1][QK];
   load_q(cu, qf);
   wait_vmcnt<0>();
   const char *kbase, *vbase;
   bool ok_cur;
   {
-    const int pg = cu.t >> 1;
+    const int pg = cu.t / TPP;
     tile_src(cu, __builtin_amdgcn_readlane(pwin, pg - pw0), kbase, vbase, ok_cur);
     for (int part = 0; part < 3; ++part) issue_part(0, cu, part, kbase, vbase);
   }
@@ -367,23 +360,21 @@ void attn_balanced_kernel(AttnParams p) {
       nu = next_unit(cu);
       pwin_n = load_window(nu.b, 0);
       if constexpr (kPrefetchQ) {
-        const bf16_t *qrow = q_row(nu, 0);
+        const T *qrow = q_row(nu, 0);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          qn[0][ks] = *reinterpret_cast<const u32x4 *>(qrow + 32 * ks + 8 * lg);
+        for (int ks = 0; ks < QK; ++ks)
+          qn[0][ks] = *reinterpret_cast<const u32x4 *>(qrow + (64 * ks + 16 * lg) / ES);
       }
     }
     reset();
     for (int t = t_first; t < t_end; ++t) {
       wait_vmcnt<0>();  // tile t, and every window and Q load issued before it
       const uint8_t *slot = ring + si * G::SLOT;
-      u32x4 kf[2][KS], vf[DT];
+      u32x4 kf[2 * KS], vf[DT];
 #pragma unroll
-      for (int e = 0; e < 2; ++e)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          kf[e][ks] = *reinterpret_cast<const u32x4 *>(slot + (e * KS + ks) * kFragBytes + 16 * lane);
-      const bool prefix_tile = t < 2 * cu.np;
+      for (int f = 0; f < 2 * KS; ++f)
+        kf[f] = *reinterpret_cast<const u32x4 *>(slot + f * kFragBytes + 16 * lane);
+      const bool prefix_tile = t < TPP * cu.np;
       int cap[NQ];
       int limit;
       bool full;
@@ -391,36 +382,27 @@ void attn_balanced_kernel(AttnParams p) {
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
           vf[dt] = *reinterpret_cast<const u32x4 *>(slot + (2 * KS + dt) * kFragBytes + 16 * lane);
-        limit = ok_cur ? min(32, cu.s - 32 * t) : 0;
-        full = limit >= 32;
+        limit = ok_cur ? min(TT, cu.s - TT * t) : 0;
+        full = limit >= TT;
         if (!full) {
           // invisible tokens enter P.V with probability 0; their values are
           // zeroed so whatever the page holds there (NaN, Inf) adds nothing
-          const int nv = min(max(limit - 8 * lg, 0), 8);
-          u32x4 keep;
-#pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4)
-            keep[q4] = (2 * q4 < nv ? 0xffffu : 0u) | (2 * q4 + 1 < nv ? 0xffff0000u : 0u);
+          const u32x4 keep = value_mask<T>(limit, lg);
 #pragma unroll
           for (int dt = 0; dt < DT; ++dt) vf[dt] &= keep;
         }
 #pragma unroll
         for (int qt = 0; qt < NQ; ++qt) cap[qt] = 0x7fffffff;
       } else {
-        // block values are token-major [32][DH] in the slot: gather V^T
-        const int ub = t - 2 * cu.np;
-        const uint16_t *raw = reinterpret_cast<const uint16_t *>(slot + 2 * KS * kFragBytes);
+        // block values are token-major [TT][DH] in the slot: gather V^T
+        const int ub = t - TPP * cu.np;
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          u16x8 v8;
-#pragma unroll
-          for (int jj = 0; jj < 8; ++jj) v8[jj] = raw[(8 * lg + jj) * DH + 16 * dt + ln];
-          vf[dt] = __builtin_bit_cast(u32x4, v8);
-        }
-        limit = p.w - 32 * ub;
+        for (int dt = 0; dt < DT; ++dt)
+          vf[dt] = gather_block_values<T, DH>(slot + 2 * KS * kFragBytes, dt, ln, lg);
+        limit = p.w - TT * ub;
         full = false;
 #pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) cap[qt] = cap_blk[qt] - 32 * ub;
+        for (int qt = 0; qt < NQ; ++qt) cap[qt] = cap_blk[qt] - TT * ub;
       }
       // the slot's fragments are in registers before the other slot is
       // refilled, and the refill below completes the previous reads
@@ -434,8 +416,8 @@ void attn_balanced_kernel(AttnParams p) {
       ci = uniform(ci);
       if (refill) {
         int page = 0;
-        if (ci.t < 2 * ci.np) {
-          const int pg = ci.t >> 1;
+        if (ci.t < TPP * ci.np) {
+          const int pg = ci.t / TPP;
           if (!in_unit) {
             page = __builtin_amdgcn_readlane(pwin_n, pg);
           } else {
@@ -455,7 +437,7 @@ void attn_balanced_kernel(AttnParams p) {
         tile_src(ci, page, kbase, vbase, ok_cur);  // ok_cur now describes tile t + 1
       }
       const int sn = si ^ 1;
-      compute_tile<DH, NQ>(st, kf, vf, qf, cap, limit, full, p.scale_log2, lg, [&](int part) {
+      compute_tile<T, DH, NQ>(st, kf, vf, qf, cap, limit, full, p.scale_log2, lg, [&](int part) {
         if (refill) issue_part(sn, ci, part, kbase, vbase);
       });
       si = sn;
@@ -475,7 +457,7 @@ void attn_balanced_kernel(AttnParams p) {
     if (t_first == 0 && lane == 0) {
       // this worker holds the unit's first tile: record where the unit's
       // pieces start and how many workers share it, for the merge
-      const long long jl = worker_of(g_unit + cu.tu - 1, T, W);
+      const long long jl = worker_of(g_unit + cu.tu - 1, tiles, W);
       const int unit = cu.b * p.hkv + cu.kvh;
       p.ws_rec[2 * unit] = unit + j;
       p.ws_rec[2 * unit + 1] = static_cast<int>(jl - j + 1);
@@ -484,7 +466,7 @@ void attn_balanced_kernel(AttnParams p) {
     remaining -= t_end - t_first;
     if (remaining <= 0) {
       if (stash_dst) {
-        const int bytes = p.rows * (DH * 2 + 16);
+        const int bytes = p.rows * (DH * rec_elem_bytes(ES) + 16);
         for (int off = 16 * lane; off < bytes; off += 1024)
           *reinterpret_cast<u32x4 *>(stash_dst + off) = *reinterpret_cast<const u32x4 *>(stash + off);
       }
@@ -496,7 +478,7 @@ void attn_balanced_kernel(AttnParams p) {
     x_pw0 = -1;
     if constexpr (kPrefetchQ) {
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) qf[0][ks] = qn[0][ks];
+      for (int ks = 0; ks < QK; ++ks) qf[0][ks] = qn[0][ks];
     } else {
       load_q(cu, qf);
     }
@@ -532,21 +514,23 @@ __global__ __launch_bounds__(kMergeThreads) void attn_balanced_combine_kernel(At
   const size_t stride = static_cast<size_t>(p.piece_stride);
   const uint8_t *rec0 = reinterpret_cast<const uint8_t *>(p.ws_o) + piece0 * stride;
   const uint8_t *orow[IT], *mrow[IT];
+  typedef typename RecVec<T>::type Ov;
+  constexpr int RB = rec_elem_bytes(sizeof(T));
   f32x4 meta[IT][kEager];
-  h16x4 ov[IT][kEager];
+  Ov ov[IT][kEager];
 #pragma unroll
   for (int it = 0; it < IT; ++it) {
     // items past the block's last repeat the first (computed, never stored)
     const int item0 = threadIdx.x + it * kMergeThreads;
     const int item = item0 < n_items ? item0 : 0;
     const int row = item / CG, c = 4 * (item % CG);
-    orow[it] = rec0 + (row * DH + c) * 2;
-    mrow[it] = rec0 + p.rows * DH * 2 + row * 16;
+    orow[it] = rec0 + (row * DH + c) * RB;
+    mrow[it] = rec0 + p.rows * DH * RB + row * 16;
 #pragma unroll
     for (int k = 0; k < kEager; ++k) {
       if (k < np) {  // uniform over the workgroup
         meta[it][k] = *reinterpret_cast<const f32x4 *>(mrow[it] + k * stride);
-        ov[it][k] = *reinterpret_cast<const h16x4 *>(orow[it] + k * stride);
+        ov[it][k] = *reinterpret_cast<const Ov *>(orow[it] + k * stride);
       }
     }
   }
@@ -572,7 +556,7 @@ __global__ __launch_bounds__(kMergeThreads) void attn_balanced_combine_kernel(At
     }
     for (int k = kEager; k < np; ++k) {
       const f32x4 mk = *reinterpret_cast<const f32x4 *>(mrow[it] + k * stride);
-      const h16x4 o = *reinterpret_cast<const h16x4 *>(orow[it] + k * stride);
+      const Ov o = *reinterpret_cast<const Ov *>(orow[it] + k * stride);
       const float nm = fmaxf(mx, mk[0]);
       const float a = exp2f(mx - nm), sc = exp2f(mk[0] - nm);
       const float w = sc * mk[2];
@@ -601,37 +585,42 @@ __global__ __launch_bounds__(kMergeThreads) void attn_balanced_combine_kernel(At
 // Blocks of up to 16 query rows: one row tile per wave; 17..32 rows: two
 // (head dims 64 and 96 only: at 128 the second tile does not fit in the
 // wave's registers, and such requests keep the split grid).
-template <int DH>
+template <typename T, int DH>
 hipError_t launch_dh(const AttnParams &p, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(p.n_workers));
   static_assert(balanced_max_rows(DH) == (DH == 128 ? 16 : 32), "launch shapes");
-  if (p.rows <= 16) return launch_kernel(attn_balanced_kernel<DH, 1>, grid, dim3(64), s, p);
+  if (p.rows <= 16) return launch_kernel(attn_balanced_kernel<T, DH, 1>, grid, dim3(64), s, p);
   if constexpr (DH == 128) return hipErrorInvalidValue;
-  else return launch_kernel(attn_balanced_kernel<DH, 2>, grid, dim3(64), s, p);
+  else return launch_kernel(attn_balanced_kernel<T, DH, 2>, grid, dim3(64), s, p);
 }
 
-template <int DH>
+template <typename T, int DH>
 hipError_t launch_combine_dh(const AttnParams &p, hipStream_t s) {
   const dim3 grid(static_cast<unsigned>(p.batch * p.hkv)), block(kMergeThreads);
   switch (merge_items<DH>(p.rows)) {
-    case 1: return launch_kernel(attn_balanced_combine_kernel<bf16_t, DH, 1>, grid, block, s, p);
-    case 2: return launch_kernel(attn_balanced_combine_kernel<bf16_t, DH, 2>, grid, block, s, p);
-    case 3: return launch_kernel(attn_balanced_combine_kernel<bf16_t, DH, 3>, grid, block, s, p);
+    case 1: return launch_kernel(attn_balanced_combine_kernel<T, DH, 1>, grid, block, s, p);
+    case 2: return launch_kernel(attn_balanced_combine_kernel<T, DH, 2>, grid, block, s, p);
+    case 3: return launch_kernel(attn_balanced_combine_kernel<T, DH, 3>, grid, block, s, p);
     default: return hipErrorInvalidValue;  // more rows than the balanced path takes
   }
 }
 
+template <typename T>
+hipError_t launch_typed(const AttnParams &p, int dh, hipStream_t s) {
+  hipError_t e;
+  if (dh == 64) e = launch_dh<T, 64>(p, s);
+  else if (dh == 96) e = launch_dh<T, 96>(p, s);
+  else e = launch_dh<T, 128>(p, s);
+  if (e != hipSuccess) return e;
+  if (dh == 64) return launch_combine_dh<T, 64>(p, s);
+  if (dh == 96) return launch_combine_dh<T, 96>(p, s);
+  return launch_combine_dh<T, 128>(p, s);
+}
+
 }  // namespace
 
-hipError_t launch_attn_balanced(const AttnParams &p, int dh, hipStream_t s) {
-  hipError_t e;
-  if (dh == 64) e = launch_dh<64>(p, s);
-  else if (dh == 96) e = launch_dh<96>(p, s);
-  else e = launch_dh<128>(p, s);
-  if (e != hipSuccess) return e;
-  if (dh == 64) return launch_combine_dh<64>(p, s);
-  if (dh == 96) return launch_combine_dh<96>(p, s);
-  return launch_combine_dh<128>(p, s);
+hipError_t launch_attn_balanced(const AttnParams &p, int dtype, int dh, hipStream_t s) {
+  return dtype == DAS_F32 ? launch_typed<float>(p, dh, s) : launch_typed<bf16_t>(p, dh, s);
 }
 
 }  // namespace das

@@ -109,10 +109,10 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(AttnParams p, int skip
 
 // The same merge over the piece records of the matrix-core kernel (one per
 // (sequence, KV head, split), piece_record_bytes each): a row's per-split
-// {m, l, q} arrive as one 16-byte vector and its outputs as fp16 values
-// scaled by q; the records of the first 24 splits are loaded together with
+// {m, l, q} arrive as one 16-byte vector and its outputs as four values
+// (fp16 or fp32) scaled by q; the records of the first 24 splits are loaded together with
 // the prefix length.
-template <int DH>
+template <typename T, int DH>
 __global__ __launch_bounds__(64) void attn_combine_records_kernel(AttnParams p, int skip_single) {
   const int unit = blockIdx.x;  // b * hkv + kvh
   const int b = unit / p.hkv;
@@ -124,17 +124,19 @@ __global__ __launch_bounds__(64) void attn_combine_records_kernel(AttnParams p, 
   const size_t stride = static_cast<size_t>(p.piece_stride);
   const uint8_t *rec0 = reinterpret_cast<const uint8_t *>(p.ws_o) +
                         static_cast<size_t>(unit) * p.nsplit * stride;
-  const uint8_t *orow = rec0 + (r0 * DH + c0) * 2;
-  const uint8_t *mrow = rec0 + static_cast<size_t>(p.rows) * DH * 2 + r0 * 16;
+  typedef typename RecVec<T>::type Ov;
+  constexpr int RB = rec_elem_bytes(sizeof(T));
+  const uint8_t *orow = rec0 + (r0 * DH + c0) * RB;
+  const uint8_t *mrow = rec0 + static_cast<size_t>(p.rows) * DH * RB + r0 * 16;
 
   const int s_raw = p.prefix_len[b];
   f32x4 meta[kEager];
-  h16x4 ov[kEager];
+  Ov ov[kEager];
 #pragma unroll
   for (int k = 0; k < kEager; ++k) {
     if (k < p.nsplit) {  // split slots of the plan (uniform); past the sequence's count: unused
       meta[k] = *reinterpret_cast<const f32x4 *>(mrow + k * stride);
-      ov[k] = *reinterpret_cast<const h16x4 *>(orow + k * stride);
+      ov[k] = *reinterpret_cast<const Ov *>(orow + k * stride);
     }
   }
   // keep every load above ahead of the first use of its result (one round trip)
@@ -165,7 +167,7 @@ __global__ __launch_bounds__(64) void attn_combine_records_kernel(AttnParams p, 
   // splits beyond the first 24, merged in the same online form
   for (int k = kEager; k < ns && live; ++k) {
     const f32x4 mk = *reinterpret_cast<const f32x4 *>(mrow + k * stride);
-    const h16x4 o = *reinterpret_cast<const h16x4 *>(orow + k * stride);
+    const Ov o = *reinterpret_cast<const Ov *>(orow + k * stride);
     const float nm = fmaxf(mx, mk[0]);
     const float a = exp2f(mx - nm), sc = exp2f(mk[0] - nm);
     const float wgt = sc * mk[2];
@@ -179,12 +181,12 @@ __global__ __launch_bounds__(64) void attn_combine_records_kernel(AttnParams p, 
   if (!write) return;
   const int i = row / p.group, g = row % p.group;
   const int h = kvh * p.group + g;
-  bf16_t *out = static_cast<bf16_t *>(p.out) + ((static_cast<size_t>(b) * p.w + i) * p.hq + h) * DH + c;
+  T *out = static_cast<T *>(p.out) + ((static_cast<size_t>(b) * p.w + i) * p.hq + h) * DH + c;
   const float inv = 1.f / den;
-  out[0] = f32_to_bf16(n0 * inv);
-  out[1] = f32_to_bf16(n1 * inv);
-  out[2] = f32_to_bf16(n2 * inv);
-  out[3] = f32_to_bf16(n3 * inv);
+  out[0] = from_f32<T>(n0 * inv);
+  out[1] = from_f32<T>(n1 * inv);
+  out[2] = from_f32<T>(n2 * inv);
+  out[3] = from_f32<T>(n3 * inv);
   if (p.lse && c == 0)
     p.lse[(static_cast<size_t>(b) * p.hq + h) * p.w + i] = (mx + log2f(den)) * 0.69314718055994530942f;
 }
@@ -196,20 +198,25 @@ hipError_t launch_typed(const AttnParams &p, int skip_single, hipStream_t s) {
   return launch_kernel(attn_combine_kernel<T, DH>, grid, dim3(64), s, p, skip_single);
 }
 
-template <int DH>
+template <typename T, int DH>
 hipError_t launch_records(const AttnParams &p, int skip_single, hipStream_t s) {
   dim3 grid(p.batch * p.hkv, (p.rows + kRowsPerBlock - 1) / kRowsPerBlock,
             (DH + kColsPerBlock - 1) / kColsPerBlock);
-  return launch_kernel(attn_combine_records_kernel<DH>, grid, dim3(64), s, p, skip_single);
+  return launch_kernel(attn_combine_records_kernel<T, DH>, grid, dim3(64), s, p, skip_single);
 }
 
 }  // namespace
 
-hipError_t launch_attn_combine_records(const AttnParams &p, int dh, int skip_single,
+hipError_t launch_attn_combine_records(const AttnParams &p, int dtype, int dh, int skip_single,
                                        hipStream_t s) {
-  if (dh == 64) return launch_records<64>(p, skip_single, s);
-  if (dh == 96) return launch_records<96>(p, skip_single, s);
-  return launch_records<128>(p, skip_single, s);
+  if (dtype == DAS_F32) {
+    if (dh == 64) return launch_records<float, 64>(p, skip_single, s);
+    if (dh == 96) return launch_records<float, 96>(p, skip_single, s);
+    return launch_records<float, 128>(p, skip_single, s);
+  }
+  if (dh == 64) return launch_records<bf16_t, 64>(p, skip_single, s);
+  if (dh == 96) return launch_records<bf16_t, 96>(p, skip_single, s);
+  return launch_records<bf16_t, 128>(p, skip_single, s);
 }
 
 hipError_t launch_attn_combine(const AttnParams &p, int dtype, int dh, int skip_single,

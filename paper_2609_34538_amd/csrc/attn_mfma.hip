@@ -73,10 +73,14 @@ __device__ __forceinline__ void prio_by_remaining(int rem) {
 // page), and one barrier per tile both publishes the tile and frees the slot
 // read in the previous iteration, which is then refilled (NB - 1 tiles in
 // flight).
-template <int DH, int NQ, int NB, int NW>
+template <typename T, int DH, int NQ, int NB, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
-  using G = Geo<DH, NQ, NB>;
+  using G = Geo<T, DH, NQ, NB>;
+  constexpr int ES = G::ES;
+  constexpr int TT = G::TT;
+  constexpr int TPP = G::TPP;
+  constexpr int QK = G::QK;
   constexpr int KS = G::KS;
   constexpr int DT = G::DT;
   constexpr int NF = G::NF;
@@ -114,23 +118,23 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
   const int pg_cap = split_first_page(split + 1, pps) - pg0;  // pages of a full split
 
   // one round trip: the prefix length, this split's page ids, the Q
-  // fragments (B operand of S^T = K Q^T: lane holds dims 8g..8g+7 of row n,
-  // loaded straight into registers)
+  // fragments (B operand of S^T = K Q^T: lane holds 16 bytes of row n per
+  // fragment, loaded straight into registers)
   const int s_raw = p.prefix_len[b];
   int page_id = 0;  // lane i: page id of the split's i-th page
   if (lane < pg_cap && pg0 + lane < p.max_pages)
     page_id = p.block_table[static_cast<size_t>(b) * p.max_pages + pg0 + lane];
-  u32x4 qf[NQ][KS];
+  u32x4 qf[NQ][QK];
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) {
     // rows past the last are clamped; their outputs are never written
     const int row = min(rt * ROWS + qt * 16 + ln, p.rows - 1);
     const int i = row / p.group, g = row % p.group;
-    const bf16_t *qrow = static_cast<const bf16_t *>(p.q) +
-                         ((static_cast<size_t>(b) * p.w + i) * p.hq + kvh * p.group + g) * DH;
+    const T *qrow = static_cast<const T *>(p.q) +
+                    ((static_cast<size_t>(b) * p.w + i) * p.hq + kvh * p.group + g) * DH;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      qf[qt][ks] = *reinterpret_cast<const u32x4 *>(qrow + 32 * ks + 8 * lg);
+    for (int ks = 0; ks < QK; ++ks)
+      qf[qt][ks] = *reinterpret_cast<const u32x4 *>(qrow + (64 * ks + 16 * lg) / ES);
   }
   bool bad;
   const int S = clamp_prefix(s_raw, p.max_pages, &bad);
@@ -146,34 +150,33 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
   // every load issued before it, prefetched tiles included).
   wait_vmcnt<0>();
   const int npg = max(0, min(pg_cap, npages - pg0));
-  const int npg2 = 2 * npg;                                   // prefix tiles
-  const int ntile = npg2 + (split == 0 ? (p.w + 31) >> 5 : 0);  // + draft-block tiles
+  const int npt = TPP * npg;                                          // prefix tiles
+  const int ntile = npt + (split == 0 ? (p.w + TT - 1) / TT : 0);  // + draft-block tiles
 
   const char *kl = static_cast<const char *>(p.k_layer);
   const char *vl = static_cast<const char *>(p.v_layer);
-  const size_t head_off = static_cast<size_t>(kvh) * p.num_pages * kPage * DH * 2;
-  const size_t tok_bytes = static_cast<size_t>(p.hkv) * DH * 2;  // block row stride
+  const size_t head_off = static_cast<size_t>(kvh) * p.num_pages * kPage * DH * ES;
+  const size_t tok_bytes = static_cast<size_t>(p.hkv) * DH * ES;  // block row stride
   const char *kblk = static_cast<const char *>(p.kb) +
-                     (static_cast<size_t>(b) * p.w * p.hkv + kvh) * DH * 2;
+                     (static_cast<size_t>(b) * p.w * p.hkv + kvh) * DH * ES;
   const char *vblk = static_cast<const char *>(p.vb) +
-                     (static_cast<size_t>(b) * p.w * p.hkv + kvh) * DH * 2;
-  // per-lane byte offsets of the fragments inside a page: key token slot
-  // 8(n/4) + n%4 (plus a uniform part), column 8g; value token group g of
-  // the tile, head dim n
-  const uint32_t lane_k = ((8 * (ln >> 2) + (ln & 3)) * DH + 8 * lg) * 2;
-  const uint32_t lane_v = (lg * DH + ln) * 16;
+                     (static_cast<size_t>(b) * p.w * p.hkv + kvh) * DH * ES;
+  // per-lane byte offsets of the fragments inside a tile's keys and values
+  // (plus a uniform part per fragment)
+  const uint32_t lane_k = G::key_lane(ln, lg);
+  const uint32_t lane_v = G::val_lane(ln, lg);
 
-  // Source of prefix tile t: its page's 32-token key half ([32][DH], at
-  // kbase) and value half (token groups 4u .. 4u + 3 of [8][DH][8], at vbase),
-  // resolved once per tile. An out-of-range page id is reported and read as
+  // Source of prefix tile t = part u of its page: TT token rows of keys
+  // ([TT][DH], at kbase) and TT / 8 token groups of values ([8][DH][8], at
+  // vbase), 64 * DH bytes each, resolved once per tile. An out-of-range page id is reported and read as
   // page 0 (its tile is masked out).
   auto tile_src = [&](int t, const char *&kbase, const char *&vbase) {
-    const int page = __builtin_amdgcn_readlane(page_id, t >> 1);
+    const int page = __builtin_amdgcn_readlane(page_id, t / TPP);
     const bool ok = page >= 0 && page < p.num_pages;
     if (!ok) report_error(p.dev_error, DAS_DEVERR_PAGE);
-    const size_t off = head_off + static_cast<size_t>(ok ? page : 0) * kPage * DH * 2;
-    const int u = t & 1;
-    kbase = kl + off + (32 * u) * DH * 2;
+    const size_t off = head_off + static_cast<size_t>(ok ? page : 0) * kPage * DH * ES;
+    const int u = t % TPP;
+    kbase = kl + off + 64 * DH * u;
     vbase = vl + off + 64 * DH * u;
   };
   // fragment f of a tile is loaded by wave f / (NF / NW): a wave's fragments
@@ -186,35 +189,36 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
   // computation of the previous tile. Both halves span 64 * DH bytes.
   auto issue_part = [&](int t, int part, const char *kbase, const char *vbase) {
     uint8_t *slot = ring + (t % NB) * G::SLOT;
-    if (t < npg2) {
+    if (t < npt) {
       if (part < 2) {
         const auto r = buffer_of(kbase, 64 * DH);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
           if (mine(part * KS + ks))
-            dma16(r, lane_k, (4 * part * DH + 32 * ks) * 2, slot + (part * KS + ks) * kFragBytes);
+            dma16(r, lane_k, G::key_frag(part * KS + ks), slot + (part * KS + ks) * kFragBytes);
       } else {
         const auto r = buffer_of(vbase, 64 * DH);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-          if (mine(2 * KS + dt)) dma16(r, lane_v, 256 * dt, slot + (2 * KS + dt) * kFragBytes);
+          if (mine(2 * KS + dt)) dma16(r, lane_v, G::val_frag(dt), slot + (2 * KS + dt) * kFragBytes);
       }
     } else {
       // draft block tile u: key fragments by token slot, value rows raw
-      const int u = t - npg2;
+      const int u = t - npt;
       if (part < 2) {
-        const int tok = min(32 * u + 8 * (ln >> 2) + 4 * part + (ln & 3), p.w - 1);
+        const int tok = min(TT * u + G::key_token(ln, part * KS), p.w - 1);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
           if (mine(part * KS + ks))
-            dma16(kblk + tok * tok_bytes + (32 * ks + 8 * lg) * 2, slot + (part * KS + ks) * kFragBytes);
+            dma16(kblk + tok * tok_bytes + G::key_col(part * KS + ks, lg),
+                  slot + (part * KS + ks) * kFragBytes);
       } else {
 #pragma unroll
         for (int f = 0; f < DT; ++f) {
           if (!mine(2 * KS + f)) continue;
-          const int o = f * kFragBytes + 16 * lane;  // byte in the [32][DH] half
-          const int tok = min(32 * u + o / (2 * DH), p.w - 1);
-          dma16(vblk + tok * tok_bytes + o % (2 * DH), slot + (2 * KS + f) * kFragBytes);
+          const int o = f * kFragBytes + 16 * lane;  // byte in the [TT][DH] rows
+          const int tok = min(TT * u + o / (ES * DH), p.w - 1);
+          dma16(vblk + tok * tok_bytes + o % (ES * DH), slot + (2 * KS + f) * kFragBytes);
         }
       }
     }
@@ -232,15 +236,15 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
       const auto r = buffer_of(kbase, 64 * DH);
 #pragma unroll
       for (int i = 0; i < FPW; ++i) {
-        const int f = f0 + i, part = f / KS, ks = f - part * KS;
-        dma16(r, lane_k, (4 * part * DH + 32 * ks) * 2, slot + f * kFragBytes);
+        const int f = f0 + i;
+        dma16(r, lane_k, G::key_frag(f), slot + f * kFragBytes);
       }
     } else {
       const auto r = buffer_of(vbase, 64 * DH);
 #pragma unroll
       for (int i = 0; i < FPW; ++i) {
         const int dt = f0 - 2 * KS + i;
-        dma16(r, lane_v, 256 * dt, slot + (2 * KS + dt) * kFragBytes);
+        dma16(r, lane_v, G::val_frag(dt), slot + (2 * KS + dt) * kFragBytes);
       }
     }
   };
@@ -248,7 +252,7 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
   int n_issued = 0;
   for (; n_issued < NB && n_issued < ntile; ++n_issued) {
     const char *kbase = kl, *vbase = vl;
-    if (n_issued < npg2) tile_src(n_issued, kbase, vbase);
+    if (n_issued < npt) tile_src(n_issued, kbase, vbase);
     for (int part = 0; part < 3; ++part) issue_part(n_issued, part, kbase, vbase);
   }
 
@@ -267,52 +271,40 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
   // Tile t's fragments from its ring slot into registers (keys; values as
   // V^T fragments, the draft block's token-major values gathered), and which
   // of its tokens each row sees.
-  auto read_tile = [&](int t, u32x4 (&kf)[2][KS], u32x4 (&vf)[DT], int (&cap)[NQ], int &limit,
+  auto read_tile = [&](int t, u32x4 (&kf)[2 * KS], u32x4 (&vf)[DT], int (&cap)[NQ], int &limit,
                        bool &full) {
     const uint8_t *slot = ring + (t % NB) * G::SLOT;
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        kf[e][ks] = *reinterpret_cast<const u32x4 *>(slot + (e * KS + ks) * kFragBytes + 16 * lane);
-    if (t < npg2) {
+    for (int f = 0; f < 2 * KS; ++f)
+      kf[f] = *reinterpret_cast<const u32x4 *>(slot + f * kFragBytes + 16 * lane);
+    if (t < npt) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
         vf[dt] = *reinterpret_cast<const u32x4 *>(slot + (2 * KS + dt) * kFragBytes + 16 * lane);
-      const int page = __builtin_amdgcn_readlane(page_id, t >> 1);
+      const int page = __builtin_amdgcn_readlane(page_id, t / TPP);
       const bool ok = page >= 0 && page < p.num_pages;
-      limit = ok ? min(32, S - (pg0 + (t >> 1)) * kPage - 32 * (t & 1)) : 0;
-      full = limit >= 32;
+      limit = ok ? min(TT, S - pg0 * kPage - TT * t) : 0;
+      full = limit >= TT;
       if (!full) {
         // Invisible tokens (past the prefix, or an unreadable page) enter P.V
         // with probability 0; their values are zeroed so that whatever the
-        // cache holds there (NaN, Inf) contributes nothing. Lane group lg
-        // holds tokens 8 lg .. 8 lg + 7 of the tile, two per 32-bit word.
-        const int nv = min(max(limit - 8 * lg, 0), 8);
-        u32x4 keep;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          keep[k] = (2 * k < nv ? 0xffffu : 0u) | (2 * k + 1 < nv ? 0xffff0000u : 0u);
+        // cache holds there (NaN, Inf) contributes nothing.
+        const u32x4 keep = value_mask<T>(limit, lg);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) vf[dt] &= keep;
       }
 #pragma unroll
       for (int qt = 0; qt < NQ; ++qt) cap[qt] = 0x7fffffff;
     } else {
-      // block values are token-major [32][DH] in the slot: gather V^T
-      const int u = t - npg2;
-      const uint16_t *raw = reinterpret_cast<const uint16_t *>(slot + 2 * KS * kFragBytes);
+      // block values are token-major [TT][DH] in the slot: gather V^T
+      const int u = t - npt;
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        u16x8 v8;
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) v8[jj] = raw[(8 * lg + jj) * DH + 16 * dt + ln];
-        vf[dt] = __builtin_bit_cast(u32x4, v8);
-      }
-      limit = p.w - 32 * u;
+      for (int dt = 0; dt < DT; ++dt)
+        vf[dt] = gather_block_values<T, DH>(slot + 2 * KS * kFragBytes, dt, ln, lg);
+      limit = p.w - TT * u;
       full = false;
 #pragma unroll
-      for (int qt = 0; qt < NQ; ++qt) cap[qt] = cap_blk[qt] - 32 * u;
+      for (int qt = 0; qt < NQ; ++qt) cap[qt] = cap_blk[qt] - TT * u;
     }
   };
 
@@ -321,7 +313,7 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
   for (int t = 0; t < ntile; ++t) {
     if (long_chunk) prio_by_remaining(ntile - t);
     wait_tiles<NF>(n_issued - t - 1);
-    u32x4 kf[2][KS], vf[DT];
+    u32x4 kf[2 * KS], vf[DT];
     int cap[NQ];
     int limit;
     bool full;
@@ -332,8 +324,8 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
     const bool refill = next < ntile;
     if (refill) ++n_issued;
     const char *kbase = kl, *vbase = vl;
-    if (refill && next < npg2) tile_src(next, kbase, vbase);
-    compute_tile<DH, NQ, true>(st, kf, vf, qf, cap, limit, full, p.scale_log2, lg, [&](int part) {
+    if (refill && next < npt) tile_src(next, kbase, vbase);
+    compute_tile<T, DH, NQ, true>(st, kf, vf, qf, cap, limit, full, p.scale_log2, lg, [&](int part) {
       if (refill) issue_part(next, part, kbase, vbase);
     });
   }
@@ -346,7 +338,7 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
     __syncthreads();
     if (t >= 1 && n_issued < ntile) {
       const char *kbase = kl, *vbase = vl;
-      if (n_issued < npg2) {
+      if (n_issued < npt) {
         tile_src(n_issued, kbase, vbase);
         issue_own_prefix(n_issued, kbase, vbase);
       } else {
@@ -354,14 +346,14 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
       }
       ++n_issued;
     }
-    u32x4 kf[2][KS], vf[DT];
+    u32x4 kf[2 * KS], vf[DT];
     int cap[NQ];
     int limit;
     bool full;
     read_tile(t, kf, vf, cap, limit, full);
     // the slot's fragments are in registers before the next barrier
     __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));  // lgkmcnt(0)
-    compute_tile<DH, NQ, true>(st, kf, vf, qf, cap, limit, full, p.scale_log2, lg, [](int) {});
+    compute_tile<T, DH, NQ, true>(st, kf, vf, qf, cap, limit, full, p.scale_log2, lg, [](int) {});
   }
 
   }
@@ -377,35 +369,26 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
     if (nsb == 1) {
       const float inv = 1.f / lrow;
       const int i = row / p.group, h = kvh * p.group + row % p.group;
-      bf16_t *orow = static_cast<bf16_t *>(p.out) +
-                     ((static_cast<size_t>(b) * p.w + i) * p.hq + h) * DH;
+      T *orow = static_cast<T *>(p.out) + ((static_cast<size_t>(b) * p.w + i) * p.hq + h) * DH;
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        const f32x4 o = st.o[qt][dt];
-        u32x2 packed;
-        packed[0] = static_cast<uint32_t>(f32_to_bf16(o[0] * inv)) |
-                    (static_cast<uint32_t>(f32_to_bf16(o[1] * inv)) << 16);
-        packed[1] = static_cast<uint32_t>(f32_to_bf16(o[2] * inv)) |
-                    (static_cast<uint32_t>(f32_to_bf16(o[3] * inv)) << 16);
-        *reinterpret_cast<u32x2 *>(orow + 16 * dt + 4 * lg) = packed;
-      }
+      for (int dt = 0; dt < DT; ++dt) store_out4(orow + 16 * dt + 4 * lg, st.o[qt][dt] * inv);
       if (lg == 0 && p.lse)
         p.lse[(static_cast<size_t>(b) * p.hq + h) * p.w + i] =
             (st.m[qt] + log2f(lrow)) * 0.69314718055994530942f;
     } else {
-      write_piece_row<DH>(prec, p.rows, row, lg, st.o[qt], st.m[qt], lrow);
+      write_piece_row<T, DH>(prec, p.rows, row, lg, st.o[qt], st.m[qt], lrow);
     }
   }
 }
 
-template <int DH, int NQ, int NB, int NW>
+template <typename T, int DH, int NQ, int NB, int NW>
 hipError_t launch_typed(const AttnParams &p, hipStream_t s) {
   const int n_rt = (p.rows + 16 * NQ - 1) / (16 * NQ);
   const int n_rg = (n_rt + NW - 1) / NW;  // row-tile groups (workgroups) per split
   // every possible chunk (the table width bounds the splits of a sequence)
   const long chunks = static_cast<long>(p.batch) * p.hkv * p.nsplit * n_rg;
   if (chunks > 0x7fffffffL) return hipErrorInvalidValue;
-  return launch_kernel(attn_mfma_kernel<DH, NQ, NB, NW>, dim3(static_cast<unsigned>(chunks)),
+  return launch_kernel(attn_mfma_kernel<T, DH, NQ, NB, NW>, dim3(static_cast<unsigned>(chunks)),
                        dim3(64 * NW), s, p, n_rg, static_cast<int>(chunks));
 }
 
@@ -415,23 +398,28 @@ hipError_t launch_typed(const AttnParams &p, hipStream_t s) {
 // waves and a 4-deep ring (two workgroups per CU; long-prefix GQA 0.33 ->
 // 0.41 of HBM peak); two row tiles: two waves and a 2-deep ring (a 4-deep
 // one would leave one wave per SIMD at head dim 128).
-template <int DH>
+template <typename T, int DH>
 hipError_t launch_dh(const AttnParams &p, hipStream_t s) {
   static_assert(mfma_tiles_per_wave(16) == 1 && mfma_tiles_per_wave(17) == 2 &&
                 mfma_waves(32) == 1 && mfma_waves(64) == 2 && mfma_waves(65) == 4,
                 "host-side grid checks mirror these shapes");
-  if (p.rows <= 16) return launch_typed<DH, 1, 2, 1>(p, s);
-  if (p.rows <= 32) return launch_typed<DH, 2, 2, 1>(p, s);
-  if (p.rows <= 64) return launch_typed<DH, 2, 2, 2>(p, s);
-  return launch_typed<DH, 2, 4, 4>(p, s);
+  if (p.rows <= 16) return launch_typed<T, DH, 1, 2, 1>(p, s);
+  if (p.rows <= 32) return launch_typed<T, DH, 2, 2, 1>(p, s);
+  if (p.rows <= 64) return launch_typed<T, DH, 2, 2, 2>(p, s);
+  return launch_typed<T, DH, 2, 4, 4>(p, s);
 }
 
 }  // namespace
 
-hipError_t launch_attn_mfma(const AttnParams &p, int dh, hipStream_t s) {
-  if (dh == 64) return launch_dh<64>(p, s);
-  if (dh == 96) return launch_dh<96>(p, s);
-  return launch_dh<128>(p, s);
+hipError_t launch_attn_mfma(const AttnParams &p, int dtype, int dh, hipStream_t s) {
+  if (dtype == DAS_F32) {
+    if (dh == 64) return launch_dh<float, 64>(p, s);
+    if (dh == 96) return launch_dh<float, 96>(p, s);
+    return launch_dh<float, 128>(p, s);
+  }
+  if (dh == 64) return launch_dh<bf16_t, 64>(p, s);
+  if (dh == 96) return launch_dh<bf16_t, 96>(p, s);
+  return launch_dh<bf16_t, 128>(p, s);
 }
 
 }  // namespace das

@@ -60,17 +60,25 @@ das_status check_batch(const das_batch *b) {
 // trips and leaves one piece per unit it shares, and the split grid's
 // chunks, dealt out by the hardware dispatcher, are faster; a single
 // sequence has nothing to balance and keeps the split grid too.
-bool balanced_pays(const das_cache *c, const das_batch *b) {
+bool balanced_pays(const das_cache *c, const das_batch *b, int rows) {
   return 8LL * b->batch * c->num_kv_heads >
-         static_cast<long long>(kNumCUs) * balanced_workers_per_cu(c->head_dim);
+         static_cast<long long>(kNumCUs) *
+             balanced_workers_per_cu(rows, c->head_dim, elem_bytes(c->dtype));
 }
 
+// fp32 requests run on the matrix cores too (full fp32 products), but for
+// narrow blocks over few tiles: a single wave streams a 16-token tile at a
+// time there, where the vector-ALU kernel's four waves share a page
+// (55 heads x 331 tokens x 1 row: 48.6 us against 45.2 for four calls; 4
+// heads x 256: 10.4 against 7.8; 55 heads x 2048, 7095 tiles: equal).
 int choose_path(const das_cache *c, const das_batch *b, int rows, const das_attn_options *o) {
   const int want = o ? o->path : DAS_PATH_AUTO;
-  if (c->dtype == DAS_F32) return DAS_PATH_VALU;
   if (want != DAS_PATH_AUTO) return want;
+  const long long units = static_cast<long long>(b->batch) * c->num_kv_heads;
+  if (c->dtype == DAS_F32 && rows <= 16 && units * b->max_pages_per_seq <= 2048)
+    return DAS_PATH_VALU;
   if (b->batch >= 2 && b->batch <= kBalancedMaxBatch && rows <= balanced_max_rows(c->head_dim) &&
-      !(o && o->pages_per_split != 0) && balanced_pays(c, b))
+      !(o && o->pages_per_split != 0) && balanced_pays(c, b, rows))
     return DAS_PATH_BALANCED;
   return DAS_PATH_MFMA;
 }
@@ -96,30 +104,22 @@ struct Plan {
 // (Measured on MI355X over 1-64 pages per split on the single-sequence,
 // ragged, long-prefix and wave-step workloads: this picks the best split
 // size on three and one within 0.5 % of the best on the fourth.)
-das_status make_plan(const das_cache *c, const das_batch *b, int hq, int w,
-                     const das_attn_options *o, Plan *plan) {
-  if (hq < 1 || hq % c->num_kv_heads != 0) return DAS_ERR_SHAPE;
-  const int group = hq / c->num_kv_heads;
-  if (group > 8) return DAS_ERR_UNSUPPORTED;
-  if (w < 1 || w > DAS_MAX_BLOCK) return DAS_ERR_SHAPE;
-  if (o && (o->pages_per_split < 0 || o->path < DAS_PATH_AUTO || o->path > DAS_PATH_BALANCED))
-    return DAS_ERR_SHAPE;
-  if (o && (o->path == DAS_PATH_MFMA || o->path == DAS_PATH_BALANCED) && c->dtype != DAS_BF16)
-    return DAS_ERR_UNSUPPORTED;
-  plan->rows = w * group;
-  plan->path = choose_path(c, b, plan->rows, o);
+das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_attn_options *o,
+                     int path, Plan *plan) {
+  const int es = elem_bytes(c->dtype);
+  plan->path = path;
   if (plan->path == DAS_PATH_BALANCED) {
     if (b->batch > kBalancedMaxBatch || plan->rows > balanced_max_rows(c->head_dim))
       return DAS_ERR_UNSUPPORTED;
     // workers: one per resident single-wave workgroup of the chip; pieces:
     // at most units + workers - 1 (index unit + worker)
-    plan->n_workers = kNumCUs * balanced_workers_per_cu(c->head_dim);
+    plan->n_workers = kNumCUs * balanced_workers_per_cu(plan->rows, c->head_dim, es);
     plan->piece_cap = b->batch * c->num_kv_heads + plan->n_workers;
     plan->pages_per_split = 0;
     plan->nsplit = 0;
     plan->nsplit_ml = 0;
-    // a piece record: the rows' fp16 outputs, then 16 bytes per row
-    plan->piece_stride = static_cast<int>(piece_record_bytes(plan->rows, c->head_dim));
+    // a piece record: the rows' outputs, then 16 bytes per row
+    plan->piece_stride = static_cast<int>(piece_record_bytes(plan->rows, c->head_dim, es));
     const size_t pieces = static_cast<size_t>(plan->piece_cap);
     plan->ws_o_bytes = pieces * plan->piece_stride;
     plan->ws_ml_bytes = 0;
@@ -152,7 +152,8 @@ das_status make_plan(const das_cache *c, const das_batch *b, int hq, int w,
     long splits = 2;
     while (splits * 2 * units <= target) splits *= 2;
     long want = maxp / splits;
-    if (want < (mfma ? 2 : 1)) want = mfma ? 2 : 1;
+    const long least = mfma && es == 2 ? 2 : 1;
+    if (want < least) want = least;
     if (want > 32) want = 32;
     pps = static_cast<int>(want);
   }
@@ -182,7 +183,7 @@ das_status make_plan(const das_cache *c, const das_batch *b, int hq, int w,
   plan->nsplit_ml = (plan->nsplit + 3) & ~3;
   if (plan->path == DAS_PATH_MFMA) {
     // one piece record per (sequence, KV head, split)
-    plan->piece_stride = static_cast<int>(piece_record_bytes(plan->rows, c->head_dim));
+    plan->piece_stride = static_cast<int>(piece_record_bytes(plan->rows, c->head_dim, es));
     plan->ws_o_bytes = static_cast<size_t>(units) * plan->nsplit * plan->piece_stride;
     plan->ws_ml_bytes = 0;
     plan->total = plan->ws_o_bytes;
@@ -197,12 +198,42 @@ das_status make_plan(const das_cache *c, const das_batch *b, int hq, int w,
   return DAS_OK;
 }
 
+// The plan of a request. `ws_bytes`: the workspace it has, SIZE_MAX when its
+// size is asked for.
+das_status make_plan(const das_cache *c, const das_batch *b, int hq, int w,
+                     const das_attn_options *o, size_t ws_bytes, Plan *plan) {
+  if (hq < 1 || hq % c->num_kv_heads != 0) return DAS_ERR_SHAPE;
+  const int group = hq / c->num_kv_heads;
+  if (group > 8) return DAS_ERR_UNSUPPORTED;
+  if (w < 1 || w > DAS_MAX_BLOCK) return DAS_ERR_SHAPE;
+  if (o && (o->pages_per_split < 0 || o->path < DAS_PATH_AUTO || o->path > DAS_PATH_BALANCED))
+    return DAS_ERR_SHAPE;
+  if (o && (o->path == DAS_PATH_MFMA || o->path == DAS_PATH_BALANCED) && c->dtype != DAS_BF16)
+    return DAS_ERR_UNSUPPORTED;
+  plan->rows = w * group;
+  const int path = choose_path(c, b, plan->rows, o);
+  if (c->dtype != DAS_F32 || path == DAS_PATH_VALU) return plan_path(c, b, w, o, path, plan);
+  // fp32 on the matrix cores: the vector-ALU kernel's bounds on the shapes
+  // hold for both, and a request whose partials do not fit the workspace it
+  // has, or pass the allocation-free entry point's scratch, where those of
+  // the vector-ALU plan (other splits) fit keeps that plan.
+  Plan matrix;
+  matrix.rows = plan->rows;
+  const das_status st = plan_path(c, b, w, o, DAS_PATH_VALU, plan);
+  if (st != DAS_OK || plan_path(c, b, w, o, path, &matrix) != DAS_OK) return st;
+  const bool misses_scratch = matrix.total > DAS_NOALLOC_SCRATCH_BYTES &&
+                              plan->total <= DAS_NOALLOC_SCRATCH_BYTES;
+  const bool misses_ws = matrix.total > ws_bytes && plan->total <= ws_bytes;
+  if (!misses_scratch && !misses_ws) *plan = matrix;
+  return DAS_OK;
+}
+
 // Validates an attention request and fills every launch parameter except the
 // workspace pointers. No HIP call.
 das_status prepare_attn(const das_cache *c, const das_batch *b, int layer, int kappa, int nu,
                         int hq, int w, const void *q, const void *kb, const void *vb,
-                        void *out, float *lse, const das_attn_options *o, AttnParams *pp,
-                        Plan *plan) {
+                        void *out, float *lse, const das_attn_options *o, size_t ws_bytes,
+                        AttnParams *pp, Plan *plan) {
   das_status st = check_cache(c);
   if (st != DAS_OK) return st;
   st = check_batch(b);
@@ -216,7 +247,7 @@ das_status prepare_attn(const das_cache *c, const das_batch *b, int layer, int k
   const int kplane = c->k_plane[kappa];
   const int vplane = c->v_plane[nu];
   if (kplane < 0 || vplane < 0) return DAS_ERR_DEPTH;
-  st = make_plan(c, b, hq, w, o, plan);
+  st = make_plan(c, b, hq, w, o, ws_bytes, plan);
   if (st != DAS_OK) return st;
 
   const int dh = c->head_dim;
@@ -268,13 +299,13 @@ das_status launch_attn(AttnParams p, const Plan &plan, int dtype, int dh, void *
   p.ws_l = reinterpret_cast<float *>(wsb + plan.ws_o_bytes + plan.ws_ml_bytes);
   p.ws_rec = reinterpret_cast<int32_t *>(wsb + plan.ws_o_bytes + 2 * plan.ws_ml_bytes);
   if (plan.path == DAS_PATH_BALANCED)
-    return launch_attn_balanced(p, dh, stream) == hipSuccess ? DAS_OK : DAS_ERR_HIP;
+    return launch_attn_balanced(p, dtype, dh, stream) == hipSuccess ? DAS_OK : DAS_ERR_HIP;
   const bool mfma = plan.path == DAS_PATH_MFMA;
-  const hipError_t e = mfma ? launch_attn_mfma(p, dh, stream)
+  const hipError_t e = mfma ? launch_attn_mfma(p, dtype, dh, stream)
                             : launch_attn_valu(p, dtype, dh, stream);
   if (e != hipSuccess) return DAS_ERR_HIP;
   // one split per sequence: the attention kernel wrote every output itself
-  if (plan.nsplit > 1 && (mfma ? launch_attn_combine_records(p, dh, 1, stream)
+  if (plan.nsplit > 1 && (mfma ? launch_attn_combine_records(p, dtype, dh, 1, stream)
                               : launch_attn_combine(p, dtype, dh, 1, stream)) != hipSuccess)
     return DAS_ERR_HIP;
   return DAS_OK;
@@ -287,7 +318,7 @@ das_status attn_common(const das_cache *c, const das_batch *b, int layer, int ka
   AttnParams p;
   Plan plan;
   const das_status st = prepare_attn(c, b, layer, kappa, nu, hq, w, q, kb, vb, out, lse, o,
-                                     &p, &plan);
+                                     ws_bytes, &p, &plan);
   if (st != DAS_OK) return st;
   if (!ws || ws_bytes < plan.total) return DAS_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(ws) % kAlign != 0) return DAS_ERR_WORKSPACE;
@@ -343,7 +374,7 @@ size_t das_attn_workspace_bytes_ex(const das_cache *cache, const das_batch *batc
                                    const das_attn_options *opts) {
   if (check_cache(cache) != DAS_OK || check_batch(batch) != DAS_OK) return 0;
   Plan plan;
-  if (make_plan(cache, batch, num_q_heads, block_len, opts, &plan) != DAS_OK) return 0;
+  if (make_plan(cache, batch, num_q_heads, block_len, opts, SIZE_MAX, &plan) != DAS_OK) return 0;
   return plan.total;
 }
 
@@ -369,7 +400,8 @@ das_status das_attn_policy_noalloc(const das_cache *cache, const das_batch *batc
   AttnParams p;
   Plan plan;
   das_status st = prepare_attn(cache, batch, layer, kappa, nu, num_q_heads, block_len, q,
-                               k_blk, v_blk, out, lse, opts, &p, &plan);
+                               k_blk, v_blk, out, lse, opts, DAS_NOALLOC_SCRATCH_BYTES, &p,
+                               &plan);
   if (st != DAS_OK) return st;
   if (plan.total > DAS_NOALLOC_SCRATCH_BYTES) return DAS_ERR_WORKSPACE;
   // the stream must belong to the current device, whose scratch copy is used

@@ -77,47 +77,61 @@ hipError_t launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStr
 
 // Launchers (return the hipError_t of the launch).
 hipError_t launch_attn_valu(const AttnParams &p, int dtype, int dh, hipStream_t s);
-hipError_t launch_attn_mfma(const AttnParams &p, int dh, hipStream_t s);
+hipError_t launch_attn_mfma(const AttnParams &p, int dtype, int dh, hipStream_t s);
 // skip_single: sequences whose prefix fits one split were already written
 // by the attention kernel (both kernel families write them directly).
 hipError_t launch_attn_combine(const AttnParams &p, int dtype, int dh, int skip_single,
                                hipStream_t s);
-// The same over the piece records the matrix-core kernel writes (bf16 output).
-hipError_t launch_attn_combine_records(const AttnParams &p, int dh, int skip_single,
+// The same over the piece records the matrix-core kernel writes.
+hipError_t launch_attn_combine_records(const AttnParams &p, int dtype, int dh, int skip_single,
                                        hipStream_t s);
 hipError_t launch_kv_append(const AppendParams &p, int dtype, int dh, hipStream_t s);
 // Balanced persistent schedule for batches of up to 64 sequences with blocks
-// of at most balanced_max_rows(dh) query rows (bf16): the attention kernel
-// and its piece merge.
-hipError_t launch_attn_balanced(const AttnParams &p, int dh, hipStream_t s);
+// of at most balanced_max_rows(dh) query rows: the attention kernel and its
+// piece merge.
+hipError_t launch_attn_balanced(const AttnParams &p, int dtype, int dh, hipStream_t s);
 constexpr int kBalancedMaxBatch = 64;
 // query rows per (sequence, KV head) the balanced kernel takes
 __host__ __device__ constexpr int balanced_max_rows(int dh) { return dh == 128 ? 16 : 32; }
-// Bytes of one piece record of the matrix-core kernels (a partial result
-// over part of a unit's positions): [rows][dh] fp16 outputs, then 16 bytes
-// per row, 256-byte aligned.
-__host__ __device__ constexpr size_t piece_record_bytes(int rows, int dh) {
-  return (static_cast<size_t>(rows) * (2 * dh + 16) + 255) / 256 * 256;
+// Bytes of one output of a piece record: fp16 for bf16 caches, fp32 for fp32.
+__host__ __device__ constexpr int rec_elem_bytes(int es) { return es; }
+// Bytes of one piece record of the matrix-core kernels (a partial result over
+// part of a unit's positions) of a cache with elements of `es` bytes:
+// [rows][dh] outputs, then 16 bytes per row, 256-byte aligned.
+__host__ __device__ constexpr size_t piece_record_bytes(int rows, int dh, int es) {
+  return (static_cast<size_t>(rows) * (rec_elem_bytes(es) * dh + 16) + 255) / 256 * 256;
 }
 constexpr int kNumCUs = 256;  // compute units of an MI355X (gfx950)
+// Query rows a balanced worker's stashed record holds: every block's on bf16
+// caches, the wave's row tiles on fp32 caches, whose records are twice the
+// size (a narrow block's worker then keeps its place in the LDS).
+__host__ __device__ constexpr int balanced_stash_rows(int rows, int dh, int es) {
+  return es == 2 ? balanced_max_rows(dh) : rows <= 16 ? 16 : 32;
+}
 // Workers of the balanced schedule per compute unit: 64 KB of tiles in flight
 // per CU, one 128 * dh-byte tile per worker, as long as every worker's LDS
 // (two ring slots and one stashed piece record) fits strictly inside the
-// 160 KB: 7 at head dim 64, 5 at 96, 4 at 128. Measured against the workers
-// whose rings alone fill the LDS (10, 6, 5): 0.78 against 0.63, 0.78 against
-// 0.78 and 0.80 against 0.60 of 8 TB/s on the DAS-Wave step's shape at each
-// head dim; when the LDS is filled exactly (head dims 64 and 128) a CU's
-// last worker is not resident with the others and runs after them.
-__host__ __device__ constexpr int balanced_lds_per_worker(int dh) {
-  return 2 * 128 * dh + static_cast<int>(piece_record_bytes(balanced_max_rows(dh), dh));
+// 160 KB: 7 at head dim 64, 5 at 96, 4 at 128 for bf16. Measured against the
+// workers whose rings alone fill the LDS (10, 6, 5): 0.78 against 0.63, 0.78
+// against 0.78 and 0.80 against 0.60 of 8 TB/s on the DAS-Wave step's shape
+// at each head dim; when the LDS is filled exactly (head dims 64 and 128) a
+// CU's last worker is not resident with the others and runs after them.
+__host__ __device__ constexpr int balanced_lds_per_worker(int rows, int dh, int es) {
+  return 2 * 128 * dh +
+         static_cast<int>(piece_record_bytes(balanced_stash_rows(rows, dh, es), dh, es));
 }
-__host__ __device__ constexpr int balanced_workers_per_cu(int dh) {
-  return 512 / dh < (160 * 1024 - 1) / balanced_lds_per_worker(dh)
+__host__ __device__ constexpr int balanced_workers_per_cu(int rows, int dh, int es) {
+  return 512 / dh < (160 * 1024 - 1) / balanced_lds_per_worker(rows, dh, es)
              ? 512 / dh
-             : (160 * 1024 - 1) / balanced_lds_per_worker(dh);
+             : (160 * 1024 - 1) / balanced_lds_per_worker(rows, dh, es);
 }
-static_assert(balanced_workers_per_cu(64) == 7 && balanced_workers_per_cu(96) == 5 &&
-                  balanced_workers_per_cu(128) == 4,
+static_assert(balanced_workers_per_cu(32, 64, 2) == 7 && balanced_workers_per_cu(32, 96, 2) == 5 &&
+                  balanced_workers_per_cu(16, 128, 2) == 4 &&
+                  balanced_workers_per_cu(16, 64, 4) == 7 &&
+                  balanced_workers_per_cu(32, 64, 4) == 6 &&
+                  balanced_workers_per_cu(16, 96, 4) == 5 &&
+                  balanced_workers_per_cu(32, 96, 4) == 4 &&
+                  balanced_workers_per_cu(16, 128, 4) == 3,
               "workers per CU of the balanced schedule");
 
 struct AcceptParams {

@@ -11,6 +11,19 @@
 //   O^T (dh x rows)    += V^T_tile (dh x tokens) . P^T (tokens x rows)
 // so a lane's 8 probabilities of one query row (after exp2 and bf16
 // rounding) are directly the B operand of the P.V product.
+//
+// fp32 caches run the same schedules on v_mfma_f32_16x16x4_f32 (full fp32
+// products and sums) over 16-token tiles, which have the bytes and the
+// fragment count of a 32-token bf16 tile. Lane layout: A[m][k]: m = n, k = g;
+// B[k][n]: k = g, n; C as above. Reduction slots may be numbered freely as
+// long as both operands agree, so each 16-byte load serves four steps: step
+// 4 j + i of S^T reduces over dims 16 j + 4 g + i, step i of O^T over tokens
+// 4 g + i, which are a lane's own four logits, so the probabilities are the B
+// operand as they stand. Bound by memory up to 32 rows (dh / 2 MFMAs of 32
+// cycles per 16 rows and tile), by the matrix cores above. Against the
+// vector-ALU kernel: 16 sequences x 55 heads x 512-4096 tokens, dh 96, 16 rows
+// 554 -> 265 us (2.9 -> 5.9 TB/s); 4 x 8 heads x 4096, dh 128, 128 rows 788 ->
+// 97 us; error against 64 bits 7.8e-7 -> 7.2e-7.
 #pragma once
 
 #include "das_internal.h"
@@ -67,6 +80,10 @@ __device__ __forceinline__ void wait_tiles(int tiles) {
   else wait_vmcnt<(3 * NF < 64 ? 3 * NF : 0)>();
 }
 
+__device__ __forceinline__ f32x4 mfma16x16x4(uint32_t a, uint32_t b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a), __uint_as_float(b), c, 0, 0, 0);
+}
+
 __device__ __forceinline__ f32x4 mfma16x16x32(u32x4 a, u32x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
@@ -97,49 +114,144 @@ __device__ __forceinline__ float group_sum(float x) {
 
 typedef _Float16 h16x4 __attribute__((ext_vector_type(4)));
 
-// One query row of a piece record (piece_record_bytes): the row's normalised
-// output O / l in fp16, scaled by 2^-e so that its largest magnitude lies in
-// [2^14, 2^15) (full fp16 precision for the row whatever the value scale,
-// half the bytes of fp32 partials), and {m, l, q = l 2^e, 0}; the merge takes
-// the row's unnormalised output as the stored values times q. m = -inf and
-// l = 0 when no position was visible (weight 0 in the merge). Lane (n, g)
-// holds head dims 16 dt + 4 g .. + 3 of the row; the 4 lanes of a row call
-// this together (the row maximum is a 4-lane reduction).
-template <int DH>
+// Four outputs of a piece record as stored.
+template <typename T> struct RecVec;
+template <> struct RecVec<bf16_t> { typedef h16x4 type; };
+template <> struct RecVec<float> { typedef f32x4 type; };
+
+// One query row of a piece record (piece_record_bytes); the merge takes the
+// row's unnormalised output as the stored values times q.
+// bf16 caches: the row's normalised output O / l in fp16, scaled by 2^-e so
+// that its largest magnitude lies in [2^14, 2^15) (full fp16 precision for the
+// row whatever the value scale, half the bytes of fp32 partials), and
+// {m, l, q = l 2^e, 0}. fp32 caches: the unnormalised output in fp32 and
+// {m, l, q = 1, 0}. m = -inf and l = 0 when no position was visible (weight 0
+// in the merge). Lane (n, g) holds head dims 16 dt + 4 g .. + 3 of the row;
+// the 4 lanes of a row call this together (the row maximum is a 4-lane
+// reduction).
+template <typename T, int DH>
 __device__ __forceinline__ void write_piece_row(uint8_t *rec, int rows, int row, int lg,
                                                 const f32x4 (&o)[DH / 16], float m, float l) {
-  const float inv = l > 0.f ? 1.f / l : 0.f;
-  float amax = 0.f;
+  float q = 1.f;
+  if constexpr (sizeof(T) == 4) {
+    float *orow = reinterpret_cast<float *>(rec) + row * DH;
 #pragma unroll
-  for (int dt = 0; dt < DH / 16; ++dt)
+    for (int dt = 0; dt < DH / 16; ++dt) *reinterpret_cast<f32x4 *>(orow + 16 * dt + 4 * lg) = o[dt];
+  } else {
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    float amax = 0.f;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) amax = fmaxf(amax, fabsf(o[dt][v]));
-  amax = group_max(amax) * inv;
-  const int e = (amax > 0.f && amax < __builtin_huge_valf()) ? __builtin_amdgcn_frexp_expf(amax) - 15 : 0;
-  const float sc = __builtin_amdgcn_ldexpf(inv, -e);
-  _Float16 *orow = reinterpret_cast<_Float16 *>(rec) + row * DH;
+    for (int dt = 0; dt < DH / 16; ++dt)
 #pragma unroll
-  for (int dt = 0; dt < DH / 16; ++dt) {
-    const h16x4 hv = {static_cast<_Float16>(o[dt][0] * sc), static_cast<_Float16>(o[dt][1] * sc),
-                      static_cast<_Float16>(o[dt][2] * sc), static_cast<_Float16>(o[dt][3] * sc)};
-    *reinterpret_cast<h16x4 *>(orow + 16 * dt + 4 * lg) = hv;
+      for (int v = 0; v < 4; ++v) amax = fmaxf(amax, fabsf(o[dt][v]));
+    amax = group_max(amax) * inv;
+    const int e = (amax > 0.f && amax < __builtin_huge_valf()) ? __builtin_amdgcn_frexp_expf(amax) - 15 : 0;
+    const float sc = __builtin_amdgcn_ldexpf(inv, -e);
+    _Float16 *orow = reinterpret_cast<_Float16 *>(rec) + row * DH;
+#pragma unroll
+    for (int dt = 0; dt < DH / 16; ++dt) {
+      const h16x4 hv = {static_cast<_Float16>(o[dt][0] * sc), static_cast<_Float16>(o[dt][1] * sc),
+                        static_cast<_Float16>(o[dt][2] * sc), static_cast<_Float16>(o[dt][3] * sc)};
+      *reinterpret_cast<h16x4 *>(orow + 16 * dt + 4 * lg) = hv;
+    }
+    q = __builtin_amdgcn_ldexpf(l, e);
   }
   if (lg == 0) {
-    const f32x4 meta = {m, l, __builtin_amdgcn_ldexpf(l, e), 0.f};
-    *reinterpret_cast<f32x4 *>(rec + static_cast<size_t>(rows) * DH * 2 + row * 16) = meta;
+    const f32x4 meta = {m, l, q, 0.f};
+    *reinterpret_cast<f32x4 *>(rec + static_cast<size_t>(rows) * DH * rec_elem_bytes(sizeof(T)) +
+                               row * 16) = meta;
   }
 }
 
-template <int DH, int NQ, int NB_>
+// Four consecutive outputs of a row in the cache's type.
+__device__ __forceinline__ void store_out4(bf16_t *dst, const f32x4 &o) {
+  u32x2 packed;
+  packed[0] = static_cast<uint32_t>(f32_to_bf16(o[0])) |
+              (static_cast<uint32_t>(f32_to_bf16(o[1])) << 16);
+  packed[1] = static_cast<uint32_t>(f32_to_bf16(o[2])) |
+              (static_cast<uint32_t>(f32_to_bf16(o[3])) << 16);
+  *reinterpret_cast<u32x2 *>(dst) = packed;
+}
+__device__ __forceinline__ void store_out4(float *dst, const f32x4 &o) {
+  *reinterpret_cast<f32x4 *>(dst) = o;
+}
+
+// Geometry of a tile of T elements: TT tokens, so that its keys and its
+// values are 64 * DH bytes each whatever the type.
+template <typename T, int DH, int NQ, int NB_>
 struct Geo {
-  static constexpr int KS = DH / 32;       // k steps of Q K^T
-  static constexpr int DT = DH / 16;       // head-dim tiles of P V
-  static constexpr int NF = 2 * KS + DT;   // fragments (loads) per 32-token tile
+  static constexpr int ES = sizeof(T);
+  static constexpr int E = 4 / ES;         // 16-token S^T tiles per tile
+  static constexpr int TT = 16 * E;        // tokens per tile
+  static constexpr int TPP = kPage / TT;   // tiles per page
+  static constexpr int KS = DH / 32;       // key fragments per issue part
+  static constexpr int QK = DH * ES / 64;  // Q fragments of a 16-row tile
+  static constexpr int DT = DH / 16;       // head-dim tiles of P V (value fragments)
+  static constexpr int NF = 2 * KS + DT;   // fragments (loads) per tile
   static constexpr int SLOT = NF * kFragBytes;
   static constexpr int NB = NB_;           // ring depth
-  static constexpr int QF = NQ * KS;       // Q fragments of a row tile
   static constexpr int LDS = NB * SLOT;
+
+  // Per-lane byte offset of a key fragment's lane inside a tile's key rows
+  // ([TT][DH]), and the uniform part of fragment f. bf16: token slot
+  // 8(n/4) + n%4 (+ 4 for the second S^T tile), dims 32 ks + 8 g .. + 7;
+  // fp32: token n, dims 16 f + 4 g .. + 3.
+  static __device__ __forceinline__ int key_token(int ln, int f) {
+    return ES == 2 ? 8 * (ln >> 2) + (ln & 3) + 4 * (f / KS) : ln;
+  }
+  static __device__ __forceinline__ uint32_t key_lane(int ln, int lg) {
+    return (ES == 2 ? 8 * (ln >> 2) + (ln & 3) : ln) * DH * ES + 16 * lg;
+  }
+  static __device__ __forceinline__ int key_frag(int f) {
+    return ES == 2 ? (4 * (f / KS) * DH + 32 * (f % KS)) * 2 : 64 * f;
+  }
+  // byte in its token's row at which a lane's piece of key fragment f starts
+  static __device__ __forceinline__ int key_col(int f, int lg) {
+    return (ES == 2 ? 64 * (f % KS) : 64 * f) + 16 * lg;
+  }
+  // The same for the values of the tile in the token-grouped page: bf16:
+  // token group g, head dim n; fp32: group g / 2, dim n, tokens 4 (g % 2) ..
+  static __device__ __forceinline__ uint32_t val_lane(int ln, int lg) {
+    return ES == 2 ? (lg * DH + ln) * 16 : ((lg >> 1) * DH + ln) * 32 + (lg & 1) * 16;
+  }
+  static __device__ __forceinline__ int val_frag(int dt) { return 128 * ES * dt; }
 };
+
+// V^T fragment dt of a draft-block tile, whose values are token-major
+// [TT][DH] in LDS: the lane's consecutive tokens of head dim 16 dt + n.
+template <typename T, int DH>
+__device__ __forceinline__ u32x4 gather_block_values(const uint8_t *raw, int dt, int ln, int lg) {
+  if constexpr (sizeof(T) == 2) {
+    const uint16_t *r = reinterpret_cast<const uint16_t *>(raw);
+    u16x8 v8;
+#pragma unroll
+    for (int jj = 0; jj < 8; ++jj) v8[jj] = r[(8 * lg + jj) * DH + 16 * dt + ln];
+    return __builtin_bit_cast(u32x4, v8);
+  } else {
+    const uint32_t *r = reinterpret_cast<const uint32_t *>(raw);
+    u32x4 v4;
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) v4[jj] = r[(4 * lg + jj) * DH + 16 * dt + ln];
+    return v4;
+  }
+}
+
+// Mask of a lane's value fragment that keeps the tile's first `limit` tokens
+// (bf16: the lane holds tokens 8 g .. + 7, two per word; fp32: 4 g .. + 3).
+template <typename T>
+__device__ __forceinline__ u32x4 value_mask(int limit, int lg) {
+  u32x4 keep;
+  if constexpr (sizeof(T) == 2) {
+    const int nv = min(max(limit - 8 * lg, 0), 8);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      keep[k] = (2 * k < nv ? 0xffffu : 0u) | (2 * k + 1 < nv ? 0xffff0000u : 0u);
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) keep[k] = 4 * lg + k < limit ? 0xffffffffu : 0u;
+  }
+  return keep;
+}
 
 template <int DH, int NQ>
 struct State {
@@ -147,60 +259,73 @@ struct State {
   f32x4 o[NQ][DH / 16];
 };
 
-// One 32-token tile through both products and the online softmax. Token t of
-// the tile (0..31) is visible when t < limit and t <= cap[qt]; a full tile
-// (every token visible) skips the mask.
+// One tile through both products and the online softmax. Token t of the tile
+// is visible when t < limit and t <= cap[qt]; a full tile (every token
+// visible) skips the mask.
 // `hook(k)` runs between the stages (k = 0 before the logits, 1 before the
 // softmax, 2 before P.V) so that the caller can spread work over the tile.
 // LANE_SUM: st.l holds this lane's share of its row's sum (alpha is the same
 // in a row's 4 lanes), which the caller reduces over the 4 lanes when it
 // writes the row; otherwise st.l holds the row's sum after every tile.
-template <int DH, int NQ, bool LANE_SUM = false, typename Hook>
-__device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf)[2][DH / 32],
+template <typename T, int DH, int NQ, bool LANE_SUM = false, typename Hook>
+__device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf)[DH / 16],
                                              const u32x4 (&vf)[DH / 16],
-                                             const u32x4 (&qf)[NQ][DH / 32],
+                                             const u32x4 (&qf)[NQ][Geo<T, DH, NQ, 1>::QK],
                                              const int (&cap)[NQ], int limit, bool full,
                                              float scale, int lg, Hook &&hook) {
-  u16x8 pf[NQ];
+  constexpr int E = Geo<T, DH, NQ, 1>::E;
+  constexpr int QK = Geo<T, DH, NQ, 1>::QK;
+  u16x8 pf[NQ];     // bf16: the probabilities as the B operand of P.V
+  f32x4 pw[NQ];     // fp32
   float alpha[NQ];
   bool moved[NQ];
-  f32x4 sacc[NQ][2];
+  f32x4 sacc[NQ][E];
   hook(0);
-  // k-step outermost: the 2 * NQ accumulators are independent, so no MFMA
+  // reduction step outermost: the accumulators are independent, so no MFMA
   // waits for the one before it
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt)
 #pragma unroll
-    for (int e = 0; e < 2; ++e) sacc[qt][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < E; ++e) sacc[qt][e] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int ks = 0; ks < DH / 32; ++ks)
+  for (int ks = 0; ks < QK; ++ks) {
+    if constexpr (sizeof(T) == 2) {
 #pragma unroll
-    for (int qt = 0; qt < NQ; ++qt)
+      for (int qt = 0; qt < NQ; ++qt)
 #pragma unroll
-      for (int e = 0; e < 2; ++e) sacc[qt][e] = mfma16x16x32(kf[e][ks], qf[qt][ks], sacc[qt][e]);
+        for (int e = 0; e < E; ++e)
+          sacc[qt][e] = mfma16x16x32(kf[e * QK + ks], qf[qt][ks], sacc[qt][e]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int qt = 0; qt < NQ; ++qt)
+          sacc[qt][0] = mfma16x16x4(kf[ks][i], qf[qt][ks][i], sacc[qt][0]);
+    }
+  }
   hook(1);
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) {
     // raw logits; masked ones are -inf. scale > 0, so the maximum of the
     // scaled logits is the scaled maximum.
-    float x[2][4];
+    float x[E][4];
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+    for (int e = 0; e < E; ++e)
 #pragma unroll
       for (int v = 0; v < 4; ++v) x[e][v] = sacc[qt][e][v];
     if (!full) {  // uniform: a full tile skips the mask
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
+      for (int e = 0; e < E; ++e) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int t = 8 * lg + 4 * e + v;
+          const int t = 4 * E * lg + 4 * e + v;
           x[e][v] = ((t < limit) & (t <= cap[qt])) ? x[e][v] : kNegInf;
         }
       }
     }
     float mx = kNegInf;
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+    for (int e = 0; e < E; ++e)
 #pragma unroll
       for (int v = 0; v < 4; ++v) mx = fmaxf(mx, x[e][v]);
     // Running maximum (base-2 units): the row's largest probability is
@@ -212,12 +337,15 @@ __device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf
     moved[qt] = alpha[qt] != 1.f;
     float psum = 0.f;
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
+    for (int e = 0; e < E; ++e) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(x[e][v], scale, neg));
         psum += pv;
-        pf[qt][4 * e + v] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(pv));
+        if constexpr (sizeof(T) == 2)
+          pf[qt][4 * e + v] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(pv));
+        else
+          pw[qt][v] = pv;
       }
     }
     if (!LANE_SUM) psum = group_sum(psum);
@@ -234,11 +362,21 @@ __device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf
       for (int dt = 0; dt < DH / 16; ++dt) st.o[qt][dt] *= alpha[qt];
     }
   }
+  if constexpr (sizeof(T) == 2) {
 #pragma unroll
-  for (int dt = 0; dt < DH / 16; ++dt) {
+    for (int dt = 0; dt < DH / 16; ++dt) {
 #pragma unroll
-    for (int qt = 0; qt < NQ; ++qt)
-      st.o[qt][dt] = mfma16x16x32(vf[dt], __builtin_bit_cast(u32x4, pf[qt]), st.o[qt][dt]);
+      for (int qt = 0; qt < NQ; ++qt)
+        st.o[qt][dt] = mfma16x16x32(vf[dt], __builtin_bit_cast(u32x4, pf[qt]), st.o[qt][dt]);
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int dt = 0; dt < DH / 16; ++dt)
+#pragma unroll
+        for (int qt = 0; qt < NQ; ++qt)
+          st.o[qt][dt] = mfma16x16x4(vf[dt][i], __float_as_uint(pw[qt][i]), st.o[qt][dt]);
   }
 }
 
