@@ -154,7 +154,9 @@ typedef enum das_attn_path {
   DAS_PATH_VALU = 1,     /* vector-ALU kernel (on fp32 caches the only path that
                             can be asked for; DAS_PATH_AUTO runs most fp32
                             requests on the matrix cores, in full fp32)      */
-  DAS_PATH_MFMA = 2,     /* matrix-core kernel over prefix splits (bf16)     */
+  DAS_PATH_MFMA = 2,     /* matrix-core kernels over prefix splits, or with
+                            pages_per_split 0 over chunks of tiles where the
+                            library finds them faster (bf16)                 */
   DAS_PATH_BALANCED = 3  /* matrix-core kernel, persistent balanced schedule:
                             every resident wave streams an equal share of
                             all sequences' tiles (bf16, 1..64 sequences,
@@ -164,7 +166,8 @@ typedef enum das_attn_path {
                             of 2..64 sequences when pages_per_split is 0
                             and the batch has more than W / 8 (sequence,
                             KV head) units, W = 256 x (7, 5, 4) workers
-                            at head_dim (64, 96, 128). */
+                            at head_dim (64, 96, 128), unless the units are
+                            short enough for one workgroup each.  */
 } das_attn_path;
 
 typedef struct das_attn_options {

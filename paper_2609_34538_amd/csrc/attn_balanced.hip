@@ -225,12 +225,12 @@ void attn_balanced_kernel(AttnParams p) {
         const auto r = buffer_of(uniform_ptr(kbase), 64 * DH);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          dma16(r, lane_k, G::key_frag(part * KS + ks), slot + (part * KS + ks) * kFragBytes);
+          dma16<kNonTemporal>(r, lane_k, G::key_frag(part * KS + ks), slot + (part * KS + ks) * kFragBytes);
       } else {
         const auto r = buffer_of(uniform_ptr(vbase), 64 * DH);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-          dma16(r, lane_v, G::val_frag(dt), slot + (2 * KS + dt) * kFragBytes);
+          dma16<kNonTemporal>(r, lane_v, G::val_frag(dt), slot + (2 * KS + dt) * kFragBytes);
       }
     } else {
       // draft block tile u: key fragments by token slot, value rows raw

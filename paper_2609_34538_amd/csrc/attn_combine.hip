@@ -107,86 +107,110 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(AttnParams p, int skip
     p.lse[(static_cast<size_t>(b) * p.hq + h) * p.w + i] = (mx + log2f(den)) * 0.69314718055994530942f;
 }
 
-// The same merge over the piece records of the matrix-core kernel (one per
-// (sequence, KV head, split), piece_record_bytes each): a row's per-split
-// {m, l, q} arrive as one 16-byte vector and its outputs as four values
-// (fp16 or fp32) scaled by q; the records of the first 24 splits are loaded together with
-// the prefix length.
-template <typename T, int DH>
-__global__ __launch_bounds__(64) void attn_combine_records_kernel(AttnParams p, int skip_single) {
+// The same merge over the piece records of the matrix-core kernels (one per
+// (sequence, KV head, split or chunk)): a row's {m, l, q} of a record arrive
+// as one 16-byte vector and its outputs as four values (fp16 or fp32)
+// scaled by q. The SG waves of a workgroup take every SG-th record, the first
+// kEagerRec of each loaded together with the prefix length, so up to
+// SG * kEagerRec records cost one memory round trip; further ones arrive in
+// batches of as many. Four waves where a plan has more than kEagerRec records
+// (measured with 34 records of 16 rows, dh 128, 8 units: 11.7 us with one wave
+// and 24 records at once, the rest one by one).
+constexpr int kEagerRec = 8;
+
+template <typename T, int DH, int SG>
+__global__ __launch_bounds__(64 * SG) void attn_combine_records_kernel(AttnParams p) {
   const int unit = blockIdx.x;  // b * hkv + kvh
   const int b = unit / p.hkv;
   const int kvh = unit % p.hkv;
-  const int row = blockIdx.y * kRowsPerBlock + threadIdx.x / 8;
-  const int c = blockIdx.z * kColsPerBlock + 4 * (threadIdx.x % 8);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row = blockIdx.y * kRowsPerBlock + lane / 8;
+  const int c = blockIdx.z * kColsPerBlock + 4 * (lane % 8);
   const bool live = row < p.rows && c < DH;
   const int r0 = live ? row : 0, c0 = live ? c : 0;
   const size_t stride = static_cast<size_t>(p.piece_stride);
+  typedef typename RecVec<T>::type Ov;
   const uint8_t *rec0 = reinterpret_cast<const uint8_t *>(p.ws_o) +
                         static_cast<size_t>(unit) * p.nsplit * stride;
-  typedef typename RecVec<T>::type Ov;
-  constexpr int RB = rec_elem_bytes(sizeof(T));
-  const uint8_t *orow = rec0 + (r0 * DH + c0) * RB;
-  const uint8_t *mrow = rec0 + static_cast<size_t>(p.rows) * DH * RB + r0 * 16;
+  const uint8_t *orow = rec0 + (r0 * DH + c0) * rec_elem_bytes(sizeof(T));
+  const uint8_t *mrow = rec0 + static_cast<size_t>(p.rows) * DH * rec_elem_bytes(sizeof(T)) + r0 * 16;
 
   const int s_raw = p.prefix_len[b];
-  f32x4 meta[kEager];
-  Ov ov[kEager];
+  f32x4 meta[kEagerRec];
+  Ov ov[kEagerRec];
+  auto load = [&](int first, int count) {
 #pragma unroll
-  for (int k = 0; k < kEager; ++k) {
-    if (k < p.nsplit) {  // split slots of the plan (uniform); past the sequence's count: unused
-      meta[k] = *reinterpret_cast<const f32x4 *>(mrow + k * stride);
-      ov[k] = *reinterpret_cast<const Ov *>(orow + k * stride);
+    for (int k = 0; k < kEagerRec; ++k) {
+      const int rec = first + SG * k;
+      if (rec < count) {  // uniform
+        meta[k] = *reinterpret_cast<const f32x4 *>(mrow + rec * stride);
+        ov[k] = *reinterpret_cast<const Ov *>(orow + rec * stride);
+      }
     }
-  }
+  };
+  load(wave, p.nsplit);  // slots of the plan; past the sequence's count: unused
   // keep every load above ahead of the first use of its result (one round trip)
   __builtin_amdgcn_sched_barrier(0);
   bool bad;
   const int S = clamp_prefix(s_raw, p.max_pages, &bad);
   const int npages = (S + kPage - 1) / kPage;
-  const int ns = splits_of(npages, p.pages_per_split);
-  const bool write = live && !(ns == 1 && skip_single);
+  constexpr int TT = 64 / sizeof(T);  // tokens per tile
+  const int ntile = (S + TT - 1) / TT + (p.w + TT - 1) / TT;
+  const int ns = p.chunk_tiles ? (ntile + p.chunk_tiles - 1) / p.chunk_tiles
+                               : splits_of(npages, p.pages_per_split);
+  if (SG > 1 && ns == 1) return;  // written by the attention kernel; uniform
 
-  // split k: maximum meta[0], sum meta[1], unnormalised output = stored * meta[2]
-  float mx = -__builtin_huge_valf();
+  // record k: maximum meta[0], sum meta[1], unnormalised output = stored * meta[2]
+  float mx = -__builtin_huge_valf(), den = 0.f;
+  f32x4 n = {0.f, 0.f, 0.f, 0.f};
+  // one wave takes the records of a plan of at most kEagerRec in one pass
+  for (int first = wave; SG == 1 ? first == 0 : first < ns; first += SG * kEagerRec) {
+    if (SG > 1 && first != wave) load(first, ns);
+    float nm = mx;
 #pragma unroll
-  for (int k = 0; k < kEager; ++k) mx = k < ns ? fmaxf(mx, meta[k][0]) : mx;
-  float den = 0.f, n0 = 0.f, n1 = 0.f, n2 = 0.f, n3 = 0.f;
+    for (int k = 0; k < kEagerRec; ++k) nm = first + SG * k < ns ? fmaxf(nm, meta[k][0]) : nm;
+    // no visible position so far: every weight is 0
+    const float ref = nm == -__builtin_huge_valf() ? 0.f : nm;
+    const float a = __builtin_amdgcn_exp2f(mx - ref);
+    den *= a;
+    n *= a;
 #pragma unroll
-  for (int k = 0; k < kEager; ++k) {
-    if (k < ns) {
-      const float sc = exp2f(meta[k][0] - mx);
-      const float wgt = sc * meta[k][2];
-      den += sc * meta[k][1];
-      n0 += wgt * static_cast<float>(ov[k][0]);
-      n1 += wgt * static_cast<float>(ov[k][1]);
-      n2 += wgt * static_cast<float>(ov[k][2]);
-      n3 += wgt * static_cast<float>(ov[k][3]);
+    for (int k = 0; k < kEagerRec; ++k) {
+      if (first + SG * k < ns) {
+        const float sc = __builtin_amdgcn_exp2f(meta[k][0] - ref);
+        const float wgt = sc * meta[k][2];
+        den += sc * meta[k][1];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) n[v] += wgt * static_cast<float>(ov[k][v]);
+      }
     }
-  }
-  // splits beyond the first 24, merged in the same online form
-  for (int k = kEager; k < ns && live; ++k) {
-    const f32x4 mk = *reinterpret_cast<const f32x4 *>(mrow + k * stride);
-    const Ov o = *reinterpret_cast<const Ov *>(orow + k * stride);
-    const float nm = fmaxf(mx, mk[0]);
-    const float a = exp2f(mx - nm), sc = exp2f(mk[0] - nm);
-    const float wgt = sc * mk[2];
-    den = den * a + sc * mk[1];
-    n0 = n0 * a + wgt * static_cast<float>(o[0]);
-    n1 = n1 * a + wgt * static_cast<float>(o[1]);
-    n2 = n2 * a + wgt * static_cast<float>(o[2]);
-    n3 = n3 * a + wgt * static_cast<float>(o[3]);
     mx = nm;
   }
-  if (!write) return;
+  if constexpr (SG > 1) {
+    __shared__ __attribute__((aligned(16))) f32x4 sn[SG][64];
+    __shared__ float smx[SG][64], sden[SG][64];
+    sn[wave][lane] = n;
+    smx[wave][lane] = mx;
+    sden[wave][lane] = den;
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int k = 1; k < SG; ++k) mx = fmaxf(mx, smx[k][lane]);
+    den = 0.f;
+    n = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < SG; ++k) {
+      const float sc = __builtin_amdgcn_exp2f(smx[k][lane] - mx);
+      den += sc * sden[k][lane];
+      n += sn[k][lane] * sc;
+    }
+  }
+  if (!live || ns == 1) return;
   const int i = row / p.group, g = row % p.group;
   const int h = kvh * p.group + g;
-  T *out = static_cast<T *>(p.out) + ((static_cast<size_t>(b) * p.w + i) * p.hq + h) * DH + c;
-  const float inv = 1.f / den;
-  out[0] = from_f32<T>(n0 * inv);
-  out[1] = from_f32<T>(n1 * inv);
-  out[2] = from_f32<T>(n2 * inv);
-  out[3] = from_f32<T>(n3 * inv);
+  store_out4(static_cast<T *>(p.out) + ((static_cast<size_t>(b) * p.w + i) * p.hq + h) * DH + c,
+             n * (1.f / den));
   if (p.lse && c == 0)
     p.lse[(static_cast<size_t>(b) * p.hq + h) * p.w + i] = (mx + log2f(den)) * 0.69314718055994530942f;
 }
@@ -199,24 +223,26 @@ hipError_t launch_typed(const AttnParams &p, int skip_single, hipStream_t s) {
 }
 
 template <typename T, int DH>
-hipError_t launch_records(const AttnParams &p, int skip_single, hipStream_t s) {
+hipError_t launch_records(const AttnParams &p, hipStream_t s) {
   dim3 grid(p.batch * p.hkv, (p.rows + kRowsPerBlock - 1) / kRowsPerBlock,
             (DH + kColsPerBlock - 1) / kColsPerBlock);
-  return launch_kernel(attn_combine_records_kernel<T, DH>, grid, dim3(64), s, p, skip_single);
+  if (p.nsplit <= kEagerRec)
+    return launch_kernel(attn_combine_records_kernel<T, DH, 1>, grid, dim3(64), s, p);
+  return launch_kernel(attn_combine_records_kernel<T, DH, 4>, grid, dim3(256), s, p);
+}
+
+template <typename T>
+hipError_t launch_records_dh(const AttnParams &p, int dh, hipStream_t s) {
+  if (dh == 64) return launch_records<T, 64>(p, s);
+  if (dh == 96) return launch_records<T, 96>(p, s);
+  return launch_records<T, 128>(p, s);
 }
 
 }  // namespace
 
-hipError_t launch_attn_combine_records(const AttnParams &p, int dtype, int dh, int skip_single,
-                                       hipStream_t s) {
-  if (dtype == DAS_F32) {
-    if (dh == 64) return launch_records<float, 64>(p, skip_single, s);
-    if (dh == 96) return launch_records<float, 96>(p, skip_single, s);
-    return launch_records<float, 128>(p, skip_single, s);
-  }
-  if (dh == 64) return launch_records<bf16_t, 64>(p, skip_single, s);
-  if (dh == 96) return launch_records<bf16_t, 96>(p, skip_single, s);
-  return launch_records<bf16_t, 128>(p, skip_single, s);
+hipError_t launch_attn_combine_records(const AttnParams &p, int dtype, int dh, hipStream_t s) {
+  return dtype == DAS_F32 ? launch_records_dh<float>(p, dh, s)
+                          : launch_records_dh<bf16_t>(p, dh, s);
 }
 
 hipError_t launch_attn_combine(const AttnParams &p, int dtype, int dh, int skip_single,

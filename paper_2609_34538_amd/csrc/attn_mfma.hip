@@ -195,12 +195,12 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
           if (mine(part * KS + ks))
-            dma16(r, lane_k, G::key_frag(part * KS + ks), slot + (part * KS + ks) * kFragBytes);
+            dma16<kNonTemporal>(r, lane_k, G::key_frag(part * KS + ks), slot + (part * KS + ks) * kFragBytes);
       } else {
         const auto r = buffer_of(vbase, 64 * DH);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-          if (mine(2 * KS + dt)) dma16(r, lane_v, G::val_frag(dt), slot + (2 * KS + dt) * kFragBytes);
+          if (mine(2 * KS + dt)) dma16<kNonTemporal>(r, lane_v, G::val_frag(dt), slot + (2 * KS + dt) * kFragBytes);
       }
     } else {
       // draft block tile u: key fragments by token slot, value rows raw
@@ -237,14 +237,14 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
 #pragma unroll
       for (int i = 0; i < FPW; ++i) {
         const int f = f0 + i;
-        dma16(r, lane_k, G::key_frag(f), slot + f * kFragBytes);
+        dma16<kNonTemporal>(r, lane_k, G::key_frag(f), slot + f * kFragBytes);
       }
     } else {
       const auto r = buffer_of(vbase, 64 * DH);
 #pragma unroll
       for (int i = 0; i < FPW; ++i) {
         const int dt = f0 - 2 * KS + i;
-        dma16(r, lane_v, G::val_frag(dt), slot + (2 * KS + dt) * kFragBytes);
+        dma16<kNonTemporal>(r, lane_v, G::val_frag(dt), slot + (2 * KS + dt) * kFragBytes);
       }
     }
   };

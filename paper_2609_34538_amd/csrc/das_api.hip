@@ -7,6 +7,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "das_internal.h"
@@ -66,11 +67,11 @@ bool balanced_pays(const das_cache *c, const das_batch *b, int rows) {
              balanced_workers_per_cu(rows, c->head_dim, elem_bytes(c->dtype));
 }
 
-// fp32 requests run on the matrix cores too (full fp32 products), but for
-// narrow blocks over few tiles: a single wave streams a 16-token tile at a
-// time there, where the vector-ALU kernel's four waves share a page
-// (55 heads x 331 tokens x 1 row: 48.6 us against 45.2 for four calls; 4
-// heads x 256: 10.4 against 7.8; 55 heads x 2048, 7095 tiles: equal).
+// fp32 requests run on the matrix cores too (full fp32 products). Narrow
+// blocks over few tiles take the vector-ALU plan, and in its place the
+// workgroup-per-chunk kernel (plan_chunks): the split grid's single waves
+// stream a 16-token tile at a time there (55 heads x 331 tokens x 1 row: split
+// grid 48.6, vector ALU 45.2, chunks 40.6 us for four calls).
 int choose_path(const das_cache *c, const das_batch *b, int rows, const das_attn_options *o) {
   const int want = o ? o->path : DAS_PATH_AUTO;
   if (want != DAS_PATH_AUTO) return want;
@@ -85,6 +86,7 @@ int choose_path(const das_cache *c, const das_batch *b, int rows, const das_attn
 
 struct Plan {
   int path;
+  int chunk_tiles;      // > 0: one workgroup per chunk of so many tiles
   int rows;             // w * G query rows per (sequence, kv head)
   int pages_per_split;
   int nsplit;
@@ -198,6 +200,92 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
   return DAS_OK;
 }
 
+// The workgroup-per-chunk kernel in place of the plan's own kernels: the units
+// (sequence, KV head, row tile of the matrix-core kernels) of a call, of
+// `tiles` tiles at most, are cut into ns chunks of kChunkWaves * k tiles, k per
+// wave. Chosen where it measured faster than the plan it replaces (uniform and
+// ragged batches of 1-48 sequences, 4-2000 units, 24-30000 tokens, both types,
+// every head dim, 1-512 rows):
+// - one chunk per unit needs no merge (5.5 us and the record traffic), but a
+//   CU takes no more than about 50 GB/s from memory, so long units need
+//   several; with k > 1 a wave waits for every tile in turn (0.75 us and its
+//   arithmetic). The estimate below, in us per call and without the launch,
+//   weighs these, the whole stream at 6.3 TB/s (lengths averaging 0.6 of the
+//   table's) and the dispatch of many workgroups. Single short sequence (55
+//   heads, 331 tokens): 8.9 -> 6.8 us; 4 x 55 heads x 512-2048: 33.5 -> 19.4.
+// - against the balanced schedule, which does not care how unequal the lengths
+//   are: units of up to 1.6 MB (4 x 55 heads x 512-4096 tokens 53.5 -> 47 us,
+//   but 1024-8192 tokens 51 against 61), and, when they do not all fit at once,
+//   up to 450 MB in all, less what the last round leaves idle (8 x 55 x
+//   512-2048 40 -> 37 us, 16 x 55 x 512-4096 131 against 141).
+// - against the split grid: 24 to 80 units of one row tile of more than 40
+//   tiles are the same or slower (55 heads x 2048 13.1 against 13.8 us, x 1024
+//   equal). Blocks of several row tiles read each tile once per row tile, from
+//   the L2 when they keep pace: at most one workgroup per CU, and only where
+//   the estimate beats the shared ring's (8-13 us + 4.5 TB/s): 16 x 8 heads x
+//   1600 tokens x 52 rows 35 -> 23 us, x 512-8192 tokens 70 against 97.
+// - in place of the vector-ALU kernel (narrow fp32 blocks over few tiles):
+//   always.
+void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes, Plan *plan) {
+  const int es = elem_bytes(c->dtype), tt = 64 / es, nq = mfma_tiles_per_wave(plan->rows);
+  const long long seq_heads = static_cast<long long>(b->batch) * c->num_kv_heads;
+  const long long all_tiles =
+      static_cast<long long>(kPage / tt) * b->max_pages_per_seq + (w + tt - 1) / tt;
+  if (seq_heads > 65536 || all_tiles > 65536) return;
+  const int n_rt = (plan->rows + 16 * nq - 1) / (16 * nq);
+  const int units = static_cast<int>(seq_heads) * n_rt, tiles = static_cast<int>(all_tiles);
+  const float tile_bytes = 128.f * c->head_dim;  // keys; the values are as many
+  const int whole_k = (tiles + kChunkWaves - 1) / kChunkWaves;  // tiles of a wave, one chunk per unit
+  const int rounds = (units + kNumCUs - 1) / kNumCUs;
+  if (plan->path == DAS_PATH_BALANCED && tiles * tile_bytes > 1.6e6f) return;
+  if (units > kNumCUs && tiles * tile_bytes * rounds * kNumCUs > 450e6f) return;
+  if (plan->path == DAS_PATH_MFMA && es == 2 && nq == 1 && units >= 24 && units <= 80 && tiles > 40)
+    return;
+
+  const float t_mem = kChunkWaves * tile_bytes / 50e3f;
+  const float t_cmp = es == 4 ? nq * c->head_dim * (16.f / 2400.f) : 0.2f * nq;
+  const float t_hbm = static_cast<float>(seq_heads) * tiles * tile_bytes / 10e6f;
+  const float t_wg = nq == 2 ? 0.0115f : 0.0065f;
+  const size_t stride = piece_record_bytes(plan->rows, c->head_dim, es);
+  auto time = [&](int k, int ns) {
+    const int m = (units * ns + kNumCUs - 1) / kNumCUs;
+    float t = k * (0.75f + t_cmp);
+    if (m * k * t_cmp > t) t = m * k * t_cmp;
+    if (m * k * t_mem > t) t = m * k * t_mem;
+    if (n_rt > 1) t *= 1.2f;
+    if (t_hbm > t) t = t_hbm;
+    if (units * ns * t_wg > t) t = units * ns * t_wg;
+    if (ns > 1) t += 5.5f + 0.02f * ns + static_cast<float>(stride * ns * seq_heads) / 1.5e6f;
+    return t;
+  };
+  // bf16 requests keep the workspace they always asked for; fp32 ones may take
+  // more where it is there, up to the allocation-free entry point's scratch
+  size_t room = plan->total;
+  if (es == 4) room = std::max(room, std::min<size_t>(ws_bytes, DAS_NOALLOC_SCRATCH_BYTES));
+  int best_k = 0, best_ns = 0;
+  float best = 0.f;
+  if (whole_k * kChunkWaves <= kChunkMaxTiles) best = time(best_k = whole_k, best_ns = 1);
+  const int most = (n_rt > 1 ? 1 : 2) * kNumCUs / units;  // chunks of a unit
+  if (most > 1) {
+    for (int k = (whole_k + most - 1) / most; k < whole_k && k * kChunkWaves <= kChunkMaxTiles; ++k) {
+      const int ns = (tiles + kChunkWaves * k - 1) / (kChunkWaves * k);
+      if (stride * ns * seq_heads <= room) {
+        const float t = time(k, ns);
+        if (!best_k || t < best) best = t, best_k = k, best_ns = ns;
+        if (units * ns <= kNumCUs) break;  // fewer chunks only take longer
+      }
+    }
+  }
+  if (!best_k) return;
+  if (plan->path == DAS_PATH_MFMA && es == 2 && n_rt > 1 &&
+      best > (n_rt > 2 ? 13.f : 9.f) + (best_ns == 1 && b->batch > 1 ? 1.35f : 2.f) * t_hbm)
+    return;
+  plan->chunk_tiles = kChunkWaves * best_k;
+  plan->nsplit = best_ns;
+  plan->piece_stride = static_cast<int>(stride);
+  if (best_ns > 1) plan->total = std::max<size_t>(plan->total, stride * best_ns * seq_heads);
+}
+
 // The plan of a request. `ws_bytes`: the workspace it has, SIZE_MAX when its
 // size is asked for.
 das_status make_plan(const das_cache *c, const das_batch *b, int hq, int w,
@@ -211,20 +299,31 @@ das_status make_plan(const das_cache *c, const das_batch *b, int hq, int w,
   if (o && (o->path == DAS_PATH_MFMA || o->path == DAS_PATH_BALANCED) && c->dtype != DAS_BF16)
     return DAS_ERR_UNSUPPORTED;
   plan->rows = w * group;
+  plan->chunk_tiles = 0;
   const int path = choose_path(c, b, plan->rows, o);
-  if (c->dtype != DAS_F32 || path == DAS_PATH_VALU) return plan_path(c, b, w, o, path, plan);
+  // where the caller leaves the kernel, or the cut of the matrix-core grid, to
+  // the library
+  const bool may_chunk = !o || ((o->path == DAS_PATH_AUTO || o->path == DAS_PATH_MFMA) &&
+                                o->pages_per_split == 0);
+  if (c->dtype != DAS_F32 || path == DAS_PATH_VALU) {
+    const das_status st = plan_path(c, b, w, o, path, plan);
+    if (st == DAS_OK && may_chunk) plan_chunks(c, b, w, ws_bytes, plan);
+    return st;
+  }
   // fp32 on the matrix cores: the vector-ALU kernel's bounds on the shapes
   // hold for both, and a request whose partials do not fit the workspace it
   // has, or pass the allocation-free entry point's scratch, where those of
   // the vector-ALU plan (other splits) fit keeps that plan.
   Plan matrix;
   matrix.rows = plan->rows;
+  matrix.chunk_tiles = 0;
   const das_status st = plan_path(c, b, w, o, DAS_PATH_VALU, plan);
   if (st != DAS_OK || plan_path(c, b, w, o, path, &matrix) != DAS_OK) return st;
   const bool misses_scratch = matrix.total > DAS_NOALLOC_SCRATCH_BYTES &&
                               plan->total <= DAS_NOALLOC_SCRATCH_BYTES;
   const bool misses_ws = matrix.total > ws_bytes && plan->total <= ws_bytes;
   if (!misses_scratch && !misses_ws) *plan = matrix;
+  if (may_chunk) plan_chunks(c, b, w, ws_bytes, plan);
   return DAS_OK;
 }
 
@@ -278,6 +377,7 @@ das_status prepare_attn(const das_cache *c, const das_batch *b, int layer, int k
   p.max_pages = b->max_pages_per_seq;
   p.pages_per_split = plan->pages_per_split;
   p.nsplit = plan->nsplit;
+  p.chunk_tiles = plan->chunk_tiles;
   p.nsplit_ml = plan->nsplit_ml;
   p.n_workers = plan->n_workers;
   p.piece_cap = plan->piece_cap;
@@ -298,15 +398,16 @@ das_status launch_attn(AttnParams p, const Plan &plan, int dtype, int dh, void *
   p.ws_m = reinterpret_cast<float *>(wsb + plan.ws_o_bytes);
   p.ws_l = reinterpret_cast<float *>(wsb + plan.ws_o_bytes + plan.ws_ml_bytes);
   p.ws_rec = reinterpret_cast<int32_t *>(wsb + plan.ws_o_bytes + 2 * plan.ws_ml_bytes);
-  if (plan.path == DAS_PATH_BALANCED)
+  if (plan.path == DAS_PATH_BALANCED && !plan.chunk_tiles)
     return launch_attn_balanced(p, dtype, dh, stream) == hipSuccess ? DAS_OK : DAS_ERR_HIP;
-  const bool mfma = plan.path == DAS_PATH_MFMA;
-  const hipError_t e = mfma ? launch_attn_mfma(p, dtype, dh, stream)
-                            : launch_attn_valu(p, dtype, dh, stream);
+  const bool valu = plan.path == DAS_PATH_VALU && !plan.chunk_tiles;
+  const hipError_t e = plan.chunk_tiles ? launch_attn_chunk(p, dtype, dh, stream)
+                       : valu           ? launch_attn_valu(p, dtype, dh, stream)
+                                        : launch_attn_mfma(p, dtype, dh, stream);
   if (e != hipSuccess) return DAS_ERR_HIP;
   // one split per sequence: the attention kernel wrote every output itself
-  if (plan.nsplit > 1 && (mfma ? launch_attn_combine_records(p, dtype, dh, 1, stream)
-                              : launch_attn_combine(p, dtype, dh, 1, stream)) != hipSuccess)
+  if (plan.nsplit > 1 && (valu ? launch_attn_combine(p, dtype, dh, 1, stream)
+                               : launch_attn_combine_records(p, dtype, dh, stream)) != hipSuccess)
     return DAS_ERR_HIP;
   return DAS_OK;
 }

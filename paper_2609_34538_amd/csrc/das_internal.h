@@ -35,6 +35,9 @@ struct AttnParams {
   int32_t pages_per_split, nsplit;
   int32_t nsplit_ml;     // nsplit rounded up to a multiple of 4 (16-byte rows of m, l)
   float scale_log2;      // log2(e) / sqrt(dh): logits in base-2 units
+  // workgroup-per-chunk kernel: tiles per chunk (0: splits of pages_per_split
+  // pages)
+  int32_t chunk_tiles;
   // balanced schedule only: workers launched (one single-wave workgroup
   // each) and the piece capacity of the workspace
   int32_t n_workers, piece_cap;
@@ -83,8 +86,12 @@ hipError_t launch_attn_mfma(const AttnParams &p, int dtype, int dh, hipStream_t 
 hipError_t launch_attn_combine(const AttnParams &p, int dtype, int dh, int skip_single,
                                hipStream_t s);
 // The same over the piece records the matrix-core kernel writes.
-hipError_t launch_attn_combine_records(const AttnParams &p, int dtype, int dh, int skip_single,
-                                       hipStream_t s);
+hipError_t launch_attn_combine_records(const AttnParams &p, int dtype, int dh, hipStream_t s);
+// One workgroup per chunk of chunk_tiles tiles (at most kChunkMaxTiles) of a
+// (sequence, KV head, row tile); the merge where a unit can span several.
+hipError_t launch_attn_chunk(const AttnParams &p, int dtype, int dh, hipStream_t s);
+constexpr int kChunkWaves = 4;
+constexpr int kChunkMaxTiles = 64 * kChunkWaves;  // a wave holds one page id per lane
 hipError_t launch_kv_append(const AppendParams &p, int dtype, int dh, hipStream_t s);
 // Balanced persistent schedule for batches of up to 64 sequences with blocks
 // of at most balanced_max_rows(dh) query rows: the attention kernel and its

@@ -52,15 +52,26 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base, in
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
 }
 
+// Cache policy of the prefix loads (aux operand of the buffer loads). Values
+// are non-temporal everywhere: prefix K/V are streamed once per call, and
+// letting them displace the L2 like reused data cost 5-10 % of the rate on
+// batched calls. A value fragment covers whole 128-byte lines; a key fragment
+// covers half of each line it touches, and a non-temporal line is gone from the
+// L1 when the fragment with its other half asks for it. Where few waves per CU
+// have to carry the stream, keys therefore use the default policy (a bare
+// stream of this pattern: 51 against 38 GB/s per CU on 55 CUs, 42 against 34
+// on 128, the same 27 on all 256); the balanced kernel, which fills the chip,
+// streams keys non-temporally too (16 sequences x 55 heads: 131 against 136 us).
+constexpr int kCached = 0, kNonTemporal = 2;
+
 // 16 bytes per lane from resource r at byte voff (per lane) + soff (uniform)
 // -> LDS at lds + 16 * lane. The uniform part travels in an SGPR, so a
-// fragment costs no vector address arithmetic. Cache policy: non-temporal
-// (nt): prefix K/V are streamed once per call, and letting them displace the
-// L2 like reused data cost 5-10 % of the rate on the batched workloads.
+// fragment costs no vector address arithmetic.
+template <int POLICY>
 __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, uint32_t voff, int soff,
                                       uint8_t *lds) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)(lds),
-                                           16, voff, soff, 0, 2);
+                                           16, voff, soff, 0, POLICY);
 }
 
 // s_waitcnt vmcnt(n), other counters untouched (gfx9 encoding).
@@ -161,6 +172,32 @@ __device__ __forceinline__ void write_piece_row(uint8_t *rec, int rows, int row,
     *reinterpret_cast<f32x4 *>(rec + static_cast<size_t>(rows) * DH * rec_elem_bytes(sizeof(T)) +
                                row * 16) = meta;
   }
+}
+
+// Four outputs (columns c .. c + 3) of a row of a piece record, from a thread
+// that holds only these: `bound` is a bound of the row's |O|, the same in
+// every thread of the row, in place of its maximum (a few powers of two too
+// large at most, and fp16 keeps full precision for 2^29 below).
+template <typename T, int DH>
+__device__ __forceinline__ void write_piece_item(uint8_t *rec, int rows, int row, int c,
+                                                 const f32x4 &o, float m, float l, float bound) {
+  float q = 1.f;
+  const size_t at = static_cast<size_t>(row) * DH + c;
+  if constexpr (sizeof(T) == 4) {
+    *reinterpret_cast<f32x4 *>(rec + at * 4) = o;
+  } else {
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    bound *= inv;
+    const int e = (bound > 0.f && bound < __builtin_huge_valf()) ? __builtin_amdgcn_frexp_expf(bound) - 15 : 0;
+    const float sc = __builtin_amdgcn_ldexpf(inv, -e);
+    *reinterpret_cast<h16x4 *>(rec + at * 2) =
+        h16x4{static_cast<_Float16>(o[0] * sc), static_cast<_Float16>(o[1] * sc),
+              static_cast<_Float16>(o[2] * sc), static_cast<_Float16>(o[3] * sc)};
+    q = __builtin_amdgcn_ldexpf(l, e);
+  }
+  if (c == 0)
+    *reinterpret_cast<f32x4 *>(rec + static_cast<size_t>(rows) * DH * rec_elem_bytes(sizeof(T)) +
+                               row * 16) = f32x4{m, l, q, 0.f};
 }
 
 // Four consecutive outputs of a row in the cache's type.
