@@ -130,7 +130,10 @@ __device__ __forceinline__ Cursor uniform(const Cursor &x) {
 template <typename T, int DH, int NQ>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_balanced_kernel(AttnParams p) {
-  using G = Geo<T, DH, NQ, 2>;
+  // whole-line key loads where they measured faster: 16 sequences x 32 heads x
+  // 512-4096 tokens, dh 128: bf16 104.6 -> 101.3 us, fp32 218 -> 208; at head
+  // dims 64 and 96 the chip-filling stream gains nothing (within 0.5 %)
+  using G = Geo<T, DH, NQ, 2, DH == 128>;
   constexpr int ES = G::ES;
   constexpr int TT = G::TT;
   constexpr int TPP = G::TPP;
@@ -175,9 +178,13 @@ void attn_balanced_kernel(AttnParams p) {
   const char *kl = static_cast<const char *>(p.k_layer);
   const char *vl = static_cast<const char *>(p.v_layer);
   const size_t tok_bytes = static_cast<size_t>(p.hkv) * DH * ES;  // block row stride
-  // per-lane byte offsets of a fragment inside a tile's keys and values (as
-  // in the split-grid kernel)
-  const uint32_t lane_k = G::key_lane(ln, lg);
+  // per-lane byte offsets of the loads inside a tile's keys and values and of
+  // the key fragments inside a slot (as in the split-grid kernel)
+  uint32_t load_k[G::LP], read_k[G::KJ];
+#pragma unroll
+  for (int i = 0; i < G::LP; ++i) load_k[i] = G::key_load(lane, i);
+#pragma unroll
+  for (int i = 0; i < G::KJ; ++i) read_k[i] = G::key_read(lane, i);
   const uint32_t lane_v = G::val_lane(ln, lg);
 
   // Q fragments of a unit (B operand of S^T = K Q^T: lane holds 16 bytes of
@@ -214,6 +221,12 @@ void attn_balanced_kernel(AttnParams p) {
     kbase = kl + off + 64 * DH * u;
     vbase = vl + off + 64 * DH * u;
   };
+  // Key load f of a tile (see the split-grid kernel).
+  auto load_key = [&](__amdgpu_buffer_rsrc_t r, int f, uint8_t *slot) {
+    uint32_t base = load_k[f % G::LP];
+    if (DH == 128) asm volatile("" : "+v"(base));
+    dma16<kNonTemporal>(r, base ^ G::key_load_xor(f), G::key_load_off(f), slot + f * kFragBytes);
+  };
   // Loads of a tile into ring slot `si`, in three parts (key fragments of
   // each S^T half, then the values) spread over the computation of the
   // previous tile.
@@ -225,7 +238,7 @@ void attn_balanced_kernel(AttnParams p) {
         const auto r = buffer_of(uniform_ptr(kbase), 64 * DH);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          dma16<kNonTemporal>(r, lane_k, G::key_frag(part * KS + ks), slot + (part * KS + ks) * kFragBytes);
+          load_key(r, part * KS + ks, slot);
       } else {
         const auto r = buffer_of(uniform_ptr(vbase), 64 * DH);
 #pragma unroll
@@ -239,11 +252,11 @@ void attn_balanced_kernel(AttnParams p) {
       const char *kblk = static_cast<const char *>(p.kb) + row0 * DH * ES;
       const char *vblk = static_cast<const char *>(p.vb) + row0 * DH * ES;
       if (part < 2) {
-        const int tok = min(TT * u + G::key_token(ln, part * KS), p.w - 1);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          dma16(kblk + tok * tok_bytes + G::key_col(part * KS + ks, lg),
-                slot + (part * KS + ks) * kFragBytes);
+        for (int f = part * KS; f < (part + 1) * KS; ++f) {
+          const int tok = min(TT * u + G::key_load_row(lane, f), p.w - 1);
+          dma16(kblk + tok * tok_bytes + G::key_load_col(lane, f), slot + f * kFragBytes);
+        }
       } else {
 #pragma unroll
         for (int f = 0; f < DT; ++f) {
@@ -373,7 +386,7 @@ void attn_balanced_kernel(AttnParams p) {
       u32x4 kf[2 * KS], vf[DT];
 #pragma unroll
       for (int f = 0; f < 2 * KS; ++f)
-        kf[f] = *reinterpret_cast<const u32x4 *>(slot + f * kFragBytes + 16 * lane);
+        kf[f] = *reinterpret_cast<const u32x4 *>(slot + read_k[G::key_read_set(f)] + G::key_read_off(f));
       const bool prefix_tile = t < TPP * cu.np;
       int cap[NQ];
       int limit;

@@ -22,8 +22,12 @@
 // tile being computed; the loads of the next tile are spread over the
 // computation of the current one. The wave waits on its own vector-memory
 // counter for the data it reads. A prefix tile's loads address a buffer
-// resource per page half with one per-lane offset and a uniform fragment
-// offset in an SGPR.
+// resource per tile with per-lane offsets and a uniform part in an SGPR; each
+// covers whole lines, and the keys' 16-byte pieces change places in their row
+// so that the fragment reads spread over the LDS banks (Geo::key_swizzle).
+// Against fetching key fragments, half of every line at a time: 16 x 8 heads x
+// 512-8192 tokens x 52 rows (dh 128) 74 -> 61 us, 40 heads x 4096 (dh 128) 22.0
+// -> 20.3, 55 heads x 4096 (dh 96) 19.8 -> 18.8, same results bit for bit.
 //
 // Both products run on v_mfma_f32_16x16x32_bf16 with the key/value tile as
 // the A operand, so softmax probabilities never leave registers:
@@ -161,9 +165,15 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
                      (static_cast<size_t>(b) * p.w * p.hkv + kvh) * DH * ES;
   const char *vblk = static_cast<const char *>(p.vb) +
                      (static_cast<size_t>(b) * p.w * p.hkv + kvh) * DH * ES;
-  // per-lane byte offsets of the fragments inside a tile's keys and values
-  // (plus a uniform part per fragment)
-  const uint32_t lane_k = G::key_lane(ln, lg);
+  // per-lane byte offsets: of a wave's key loads inside a tile's keys, of the
+  // key fragments inside a slot, of the value fragments inside a tile's values
+  constexpr int FPW = NF / NW;  // fragments of a tile that a wave loads
+  const int f0 = wave * FPW;
+  uint32_t load_k[G::LP], read_k[G::KJ];
+#pragma unroll
+  for (int i = 0; i < G::LP; ++i) load_k[i] = G::key_load(lane, i);
+#pragma unroll
+  for (int j = 0; j < G::KJ; ++j) read_k[j] = G::key_read(lane, j);
   const uint32_t lane_v = G::val_lane(ln, lg);
 
   // Source of prefix tile t = part u of its page: TT token rows of keys
@@ -178,6 +188,13 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
     const int u = t % TPP;
     kbase = kl + off + 64 * DH * u;
     vbase = vl + off + 64 * DH * u;
+  };
+  // Key load f of a tile. At head dim 128 the registers are tight: the offset
+  // is made from the base for every load instead of being kept.
+  auto load_key = [&](__amdgpu_buffer_rsrc_t r, int f, uint8_t *slot) {
+    uint32_t base = load_k[f % G::LP];
+    if (DH == 128) asm volatile("" : "+v"(base));
+    dma16<kNonTemporal>(r, base ^ G::key_load_xor(f), G::key_load_off(f), slot + f * kFragBytes);
   };
   // fragment f of a tile is loaded by wave f / (NF / NW): a wave's fragments
   // cover whole 128-byte lines (the key fragments of one S^T half are the
@@ -194,24 +211,23 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
         const auto r = buffer_of(kbase, 64 * DH);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          if (mine(part * KS + ks))
-            dma16<kNonTemporal>(r, lane_k, G::key_frag(part * KS + ks), slot + (part * KS + ks) * kFragBytes);
+          load_key(r, part * KS + ks, slot);
       } else {
         const auto r = buffer_of(vbase, 64 * DH);
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
-          if (mine(2 * KS + dt)) dma16<kNonTemporal>(r, lane_v, G::val_frag(dt), slot + (2 * KS + dt) * kFragBytes);
+          dma16<kNonTemporal>(r, lane_v, G::val_frag(dt), slot + (2 * KS + dt) * kFragBytes);
       }
     } else {
       // draft block tile u: key fragments by token slot, value rows raw
       const int u = t - npt;
       if (part < 2) {
-        const int tok = min(TT * u + G::key_token(ln, part * KS), p.w - 1);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          if (mine(part * KS + ks))
-            dma16(kblk + tok * tok_bytes + G::key_col(part * KS + ks, lg),
-                  slot + (part * KS + ks) * kFragBytes);
+        for (int f = part * KS; f < (part + 1) * KS; ++f) {
+          if (!mine(f)) continue;
+          const int tok = min(TT * u + G::key_load_row(lane, f), p.w - 1);
+          dma16(kblk + tok * tok_bytes + G::key_load_col(lane, f), slot + f * kFragBytes);
+        }
       } else {
 #pragma unroll
         for (int f = 0; f < DT; ++f) {
@@ -228,16 +244,14 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
   // fragments, which is whole key halves or whole value groups, so the
   // fragment offsets are scalars and no per-fragment test is made.
   auto issue_own_prefix = [&](int t, const char *kbase, const char *vbase) {
-    constexpr int FPW = NF / NW;
     static_assert(NW == 1 || (2 * KS) % FPW == 0, "a wave loads keys only or values only");
     uint8_t *slot = ring + (t % NB) * G::SLOT;
-    const int f0 = wave * FPW;
     if (f0 < 2 * KS) {
       const auto r = buffer_of(kbase, 64 * DH);
 #pragma unroll
       for (int i = 0; i < FPW; ++i) {
         const int f = f0 + i;
-        dma16<kNonTemporal>(r, lane_k, G::key_frag(f), slot + f * kFragBytes);
+        load_key(r, f, slot);
       }
     } else {
       const auto r = buffer_of(vbase, 64 * DH);
@@ -253,7 +267,11 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
   for (; n_issued < NB && n_issued < ntile; ++n_issued) {
     const char *kbase = kl, *vbase = vl;
     if (n_issued < npt) tile_src(n_issued, kbase, vbase);
-    for (int part = 0; part < 3; ++part) issue_part(n_issued, part, kbase, vbase);
+    if (NW > 1 && n_issued < npt) {
+      issue_own_prefix(n_issued, kbase, vbase);
+    } else {
+      for (int part = 0; part < 3; ++part) issue_part(n_issued, part, kbase, vbase);
+    }
   }
 
   int cap_blk[NQ];
@@ -276,7 +294,7 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
     const uint8_t *slot = ring + (t % NB) * G::SLOT;
 #pragma unroll
     for (int f = 0; f < 2 * KS; ++f)
-      kf[f] = *reinterpret_cast<const u32x4 *>(slot + f * kFragBytes + 16 * lane);
+      kf[f] = *reinterpret_cast<const u32x4 *>(slot + read_k[G::key_read_set(f)] + G::key_read_off(f));
     if (t < npt) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)

@@ -57,11 +57,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *base, in
 // letting them displace the L2 like reused data cost 5-10 % of the rate on
 // batched calls. A value fragment covers whole 128-byte lines; a key fragment
 // covers half of each line it touches, and a non-temporal line is gone from the
-// L1 when the fragment with its other half asks for it. Where few waves per CU
-// have to carry the stream, keys therefore use the default policy (a bare
-// stream of this pattern: 51 against 38 GB/s per CU on 55 CUs, 42 against 34
-// on 128, the same 27 on all 256); the balanced kernel, which fills the chip,
-// streams keys non-temporally too (16 sequences x 55 heads: 131 against 136 us).
+// L1 when the fragment with its other half asks for it. Kernels that load key
+// fragments straight into registers therefore use the default policy for them
+// (a bare stream of this pattern: 51 against 38 GB/s per CU on 55 CUs, 42
+// against 34 on 128, the same 27 on all 256); those that stage tiles in LDS
+// load whole lines, non-temporally (default policy: 16 sequences x 55 heads
+// 136 against 131 us).
 constexpr int kCached = 0, kNonTemporal = 2;
 
 // 16 bytes per lane from resource r at byte voff (per lane) + soff (uniform)
@@ -214,8 +215,9 @@ __device__ __forceinline__ void store_out4(float *dst, const f32x4 &o) {
 }
 
 // Geometry of a tile of T elements: TT tokens, so that its keys and its
-// values are 64 * DH bytes each whatever the type.
-template <typename T, int DH, int NQ, int NB_>
+// values are 64 * DH bytes each whatever the type. LINES: how a kernel that
+// stages tiles in LDS holds the keys there (see key_swizzle).
+template <typename T, int DH, int NQ, int NB_, bool LINES = true>
 struct Geo {
   static constexpr int ES = sizeof(T);
   static constexpr int E = 4 / ES;         // 16-token S^T tiles per tile
@@ -239,13 +241,67 @@ struct Geo {
   static __device__ __forceinline__ uint32_t key_lane(int ln, int lg) {
     return (ES == 2 ? 8 * (ln >> 2) + (ln & 3) : ln) * DH * ES + 16 * lg;
   }
-  static __device__ __forceinline__ int key_frag(int f) {
+  static __device__ __forceinline__ constexpr int key_frag(int f) {
     return ES == 2 ? (4 * (f / KS) * DH + 32 * (f % KS)) * 2 : 64 * f;
   }
   // byte in its token's row at which a lane's piece of key fragment f starts
   static __device__ __forceinline__ int key_col(int f, int lg) {
     return (ES == 2 ? 64 * (f % KS) : 64 * f) + 16 * lg;
   }
+  // Keys in LDS, LINES: the direct-to-LDS loads of a tile's keys read its rows
+  // as they lie in memory, whole lines per instruction, so the slot holds the
+  // rows in order; to spread the lanes that read a fragment (16 rows, 4
+  // neighbouring 16-byte pieces) over the banks, the pieces of a row change
+  // places inside its 64, 128 or 256 bytes by an exclusive or with
+  // key_swizzle(row). Otherwise a load fetches a fragment, which the slot holds
+  // lane by lane; it asks for half of each line at a time, 38 against 54 GB/s
+  // per CU on 55 CUs, 24.8 against 26.0 on 256 with four waves each.
+  static constexpr int CPR = DH * ES / 16;  // 16-byte pieces of a row
+  static __device__ __forceinline__ int key_swizzle(int row) {
+    if (ES == 2) {
+      if (DH == 96) return (row >> 3) & 3;
+      return (DH == 64 ? (row >> 1) & 1 : row & 3) * 4 + ((row >> 3) & 3);
+    }
+    return (DH == 96 ? (row >> 1) & 1 : row & 3) * 4 + ((row >> 2) & 3);
+  }
+  // row of the tile and byte in that row that lane `lane` of key load f fetches
+  static __device__ __forceinline__ int key_load_row(int lane, int f) {
+    return LINES ? (64 * f + lane) / CPR : key_token(lane & 15, f);
+  }
+  static __device__ __forceinline__ int key_load_col(int lane, int f) {
+    return LINES ? (((64 * f + lane) % CPR) ^ key_swizzle(key_load_row(lane, f))) * 16
+                 : key_col(f, lane >> 4);
+  }
+  // byte in the tile's keys: key_load(lane, f % LP) of the first LP loads
+  // carries every lane-dependent part, (.. ^ key_load_xor(f)) + key_load_off(f)
+  // is load f's
+  static constexpr int LP = LINES && DH == 96 ? 3 : 1;
+  static __device__ __forceinline__ uint32_t key_load(int lane, int f) {
+    return key_load_row(lane, f) * (DH * ES) + key_load_col(lane, f);
+  }
+  static __device__ __forceinline__ constexpr int key_load_xor(int f) {
+    if (!LINES) return 0;
+    if (DH == 96) return 16 * 2 * (f / 3);
+    if (DH == 64) return 16 * f;
+    return 16 * (ES == 4 ? 8 * (f & 1) + (f >> 1) : f >> 1);
+  }
+  static __device__ __forceinline__ constexpr int key_load_off(int f) {
+    return LINES ? (f - f % LP) * 1024 : key_frag(f);
+  }
+  // byte of the slot at which a lane reads its piece of fragment f:
+  // key_read(lane, key_read_set(f)) + key_read_off(f)
+  static constexpr int KJ = !LINES ? 1 : DH == 96 ? (ES == 2 ? 1 : 2) : (ES == 2 && DH == 64 ? 2 : 4);
+  static __device__ __forceinline__ uint32_t key_read(int lane, int set) {
+    if (!LINES) return 16 * lane;
+    const int row = key_token(lane & 15, 0);
+    return (row * CPR + ((4 * set + (lane >> 4)) ^ key_swizzle(row))) * 16;
+  }
+  static constexpr int key_read_set(int f) { return (ES == 2 ? f % KS : f) % KJ; }
+  static constexpr int key_read_off(int f) {
+    if (!LINES) return f * kFragBytes;
+    return ES == 2 ? (f / KS) * 64 * CPR + (f % KS - f % KS % KJ) * 64 : (f - f % KJ) * 64;
+  }
+
   // The same for the values of the tile in the token-grouped page: bf16:
   // token group g, head dim n; fp32: group g / 2, dim n, tokens 4 (g % 2) ..
   static __device__ __forceinline__ uint32_t val_lane(int ln, int lg) {
