@@ -124,7 +124,7 @@ __global__ __launch_bounds__(64 * SG) void attn_combine_records_kernel(AttnParam
   const int b = unit / p.hkv;
   const int kvh = unit % p.hkv;
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = SG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int row = blockIdx.y * kRowsPerBlock + lane / 8;
   const int c = blockIdx.z * kColsPerBlock + 4 * (lane % 8);
   const bool live = row < p.rows && c < DH;

@@ -218,12 +218,15 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
 //   but 1024-8192 tokens 51 against 61), and, when they do not all fit at once,
 //   up to 450 MB in all, less what the last round leaves idle (8 x 55 x
 //   512-2048 40 -> 37 us, 16 x 55 x 512-4096 131 against 141).
-// - against the split grid: 24 to 80 units of one row tile of more than 40
-//   tiles are the same or slower (55 heads x 2048 13.1 against 13.8 us, x 1024
-//   equal). Blocks of several row tiles read each tile once per row tile, from
-//   the L2 when they keep pace: at most one workgroup per CU, and only where
-//   the estimate beats the shared ring's (8-13 us + 4.5 TB/s): 16 x 8 heads x
-//   1600 tokens x 52 rows 35 -> 23 us, x 512-8192 tokens 70 against 97.
+// - against the split grid, blocks of one row tile: always (55 heads x 2000
+//   tokens, dh 96, 13.6 -> 12.7 us; 45 x 22698, dh 128, 88 -> 78; 32 heads x
+//   1300 10.7 -> 8.9). Blocks of several row tiles read each tile once per row
+//   tile, from the L2 as long as they keep pace (18 tiles per wave; 55 heads x
+//   9000 tokens, 36 per wave, 52 against 65 us): at most one workgroup per CU
+//   where a unit has several chunks, and only where
+//   the estimate beats the shared ring's: 16 x 8 heads x 1000 tokens x 52 rows,
+//   dh 128, 28.6 -> 17.9 us, x 512-8192 tokens 61 against 97; 4 x 8 heads x
+//   300 tokens x 100 rows 12.7 -> 9.8, x 2500 20-25 us either way.
 // - in place of the vector-ALU kernel (narrow fp32 blocks over few tiles):
 //   always.
 void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes, Plan *plan) {
@@ -239,8 +242,6 @@ void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes,
   const int rounds = (units + kNumCUs - 1) / kNumCUs;
   if (plan->path == DAS_PATH_BALANCED && tiles * tile_bytes > 1.6e6f) return;
   if (units > kNumCUs && tiles * tile_bytes * rounds * kNumCUs > 450e6f) return;
-  if (plan->path == DAS_PATH_MFMA && es == 2 && nq == 1 && units >= 24 && units <= 80 && tiles > 40)
-    return;
 
   const float t_mem = kChunkWaves * tile_bytes / 50e3f;
   const float t_cmp = es == 4 ? nq * c->head_dim * (16.f / 2400.f) : 0.2f * nq;
@@ -252,7 +253,7 @@ void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes,
     float t = k * (0.75f + t_cmp);
     if (m * k * t_cmp > t) t = m * k * t_cmp;
     if (m * k * t_mem > t) t = m * k * t_mem;
-    if (n_rt > 1) t *= 1.2f;
+    if (n_rt > 1) t *= 1.1f;
     if (t_hbm > t) t = t_hbm;
     if (units * ns * t_wg > t) t = units * ns * t_wg;
     if (ns > 1) t += 5.5f + 0.02f * ns + static_cast<float>(stride * ns * seq_heads) / 1.5e6f;
@@ -277,9 +278,12 @@ void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes,
     }
   }
   if (!best_k) return;
-  if (plan->path == DAS_PATH_MFMA && es == 2 && n_rt > 1 &&
-      best > (n_rt > 2 ? 13.f : 9.f) + (best_ns == 1 && b->batch > 1 ? 1.35f : 2.f) * t_hbm)
-    return;
+  if (plan->path == DAS_PATH_MFMA && es == 2 && n_rt > 1) {
+    // the shared ring: launch, merge and the stream at 4.2 or 3 TB/s (the
+    // lengths of a batch vary; chunks of a unit suffer less from that)
+    const float slope = b->batch == 1 ? 2.4f : best_ns > 1 ? 1.9f : 1.45f;
+    if (best_k > 18 || best + 3.f > (n_rt == 2 ? 8.5f + slope * t_hbm : 9.5f + 1.38f * slope * t_hbm)) return;
+  }
   plan->chunk_tiles = kChunkWaves * best_k;
   plan->nsplit = best_ns;
   plan->piece_stride = static_cast<int>(stride);
