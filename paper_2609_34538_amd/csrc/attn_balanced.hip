@@ -130,10 +130,11 @@ __device__ __forceinline__ Cursor uniform(const Cursor &x) {
 template <typename T, int DH, int NQ>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_balanced_kernel(AttnParams p) {
-  // whole-line key loads where they measured faster: 16 sequences x 32 heads x
-  // 512-4096 tokens, dh 128: bf16 104.6 -> 101.3 us, fp32 218 -> 208; at head
-  // dims 64 and 96 the chip-filling stream gains nothing (within 0.5 %)
-  using G = Geo<T, DH, NQ, 2, DH == 128>;
+  // whole-line key loads where they measured faster: fp32 at head dim 128 (16
+  // sequences x 32 heads x 512-4096 tokens 219 -> 210 us, 8 x 32 x 4000 186 ->
+  // 177); elsewhere the chip-filling stream gains nothing (bf16, dh 128: +2 % to
+  // -2 %, dh 64 and 96 within 0.5 %)
+  using G = Geo<T, DH, NQ, 2, sizeof(T) == 4 && DH == 128>;
   constexpr int ES = G::ES;
   constexpr int TT = G::TT;
   constexpr int TPP = G::TPP;

@@ -206,7 +206,7 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
 // wave. Chosen where it measured faster than the plan it replaces (uniform and
 // ragged batches of 1-48 sequences, 4-2000 units, 24-30000 tokens, both types,
 // every head dim, 1-512 rows):
-// - one chunk per unit needs no merge (5.5 us and the record traffic), but a
+// - one chunk per unit needs no merge (5.2 us and the record traffic), but a
 //   CU takes no more than about 50 GB/s from memory, so long units need
 //   several; with k > 1 a wave waits for every tile in turn (0.75 us and its
 //   arithmetic). The estimate below, in us per call and without the launch,
@@ -217,10 +217,15 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
 //   are: units of up to 1.6 MB (4 x 55 heads x 512-4096 tokens 53.5 -> 47 us,
 //   but 1024-8192 tokens 51 against 61), and, when they do not all fit at once,
 //   up to 450 MB in all, less what the last round leaves idle (8 x 55 x
-//   512-2048 40 -> 37 us, 16 x 55 x 512-4096 131 against 141).
-// - against the split grid, blocks of one row tile: always (55 heads x 2000
-//   tokens, dh 96, 13.6 -> 12.7 us; 45 x 22698, dh 128, 88 -> 78; 32 heads x
-//   1300 10.7 -> 8.9). Blocks of several row tiles read each tile once per row
+//   512-2048 40 -> 37 us, 16 x 55 x 512-4096 131 against 141); the same while
+//   the split grid's units fill one to two rounds (48 x 8 heads x 500-4096, dh
+//   128, 32 rows 94 against 111). fp32 blocks of two row tiles are bound by
+//   the matrix cores and gain from two waves per SIMD: 16 x 55 heads x 512-4096
+//   x 32 rows 355 -> 328 us.
+// - against the split grid, blocks of one row tile: otherwise always (55 heads
+//   x 2000 tokens, dh 96, 13.6 -> 12.7 us; 45 x 22698, dh 128, 88 -> 78; 32
+//   heads x 1300 10.7 -> 8.9; 512 units x 1024-8192, dh 128, 20 rows, 239 ->
+//   200; fp32 512 units x 512-4096, dh 128, 32 rows 498 -> 261). Blocks of several row tiles read each tile once per row
 //   tile, from the L2 as long as they keep pace (18 tiles per wave; 55 heads x
 //   9000 tokens, 36 per wave, 52 against 65 us): at most one workgroup per CU
 //   where a unit has several chunks, and only where
@@ -240,11 +245,16 @@ void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes,
   const float tile_bytes = 128.f * c->head_dim;  // keys; the values are as many
   const int whole_k = (tiles + kChunkWaves - 1) / kChunkWaves;  // tiles of a wave, one chunk per unit
   const int rounds = (units + kNumCUs - 1) / kNumCUs;
-  if (plan->path == DAS_PATH_BALANCED && tiles * tile_bytes > 1.6e6f) return;
-  if (units > kNumCUs && tiles * tile_bytes * rounds * kNumCUs > 450e6f) return;
+  const bool f32_wide = es == 4 && nq == 2;
+  if (plan->path == DAS_PATH_BALANCED && tiles * tile_bytes > 1.6e6f &&
+      !(f32_wide && units >= 2 * kNumCUs))
+    return;
+  if (units > kNumCUs && !f32_wide && (plan->path != DAS_PATH_MFMA || units < 2 * kNumCUs) &&
+      tiles * tile_bytes * rounds * kNumCUs > 450e6f)
+    return;
 
   const float t_mem = kChunkWaves * tile_bytes / 50e3f;
-  const float t_cmp = es == 4 ? nq * c->head_dim * (16.f / 2400.f) : 0.2f * nq;
+  const float t_cmp = nq * c->head_dim * (es == 4 ? 16.f / 2400.f : 0.27f / 100.f);
   const float t_hbm = static_cast<float>(seq_heads) * tiles * tile_bytes / 10e6f;
   const float t_wg = nq == 2 ? 0.0115f : 0.0065f;
   const size_t stride = piece_record_bytes(plan->rows, c->head_dim, es);
@@ -256,7 +266,7 @@ void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes,
     if (n_rt > 1) t *= 1.1f;
     if (t_hbm > t) t = t_hbm;
     if (units * ns * t_wg > t) t = units * ns * t_wg;
-    if (ns > 1) t += 5.5f + 0.02f * ns + static_cast<float>(stride * ns * seq_heads) / 1.5e6f;
+    if (ns > 1) t += 5.2f + 0.02f * ns + static_cast<float>(stride * ns * seq_heads) / 1.5e6f;
     return t;
   };
   // bf16 requests keep the workspace they always asked for; fp32 ones may take
