@@ -2,18 +2,25 @@
 // (Sec. 3.4: full-depth K/V of accepted, materialised inputs are retained;
 // App. B.1: draft-side K/V never enter the cache).
 //
-// One wave per (plane, layer, KV head) of one sequence, four per workgroup,
-// all of one sequence so the commit count n is uniform in the workgroup, and
-// all keys or all values (the value waves share barriers).
-// The wave reads the sequence's length, count and the (at most two) page ids
-// its n new positions fall in once, then
+// One wave per (plane, layer, KV head) of one sequence, four independent waves
+// per workgroup, all keys or all values. The wave reads the sequence's length,
+// count and the (at most two) page ids its n new positions fall in once, then
 //  - keys: copies the n token rows with 16-byte vectors (rows of head_dim
 //    are contiguous in both the source and the token-major page);
-//  - values: stages up to 16 token rows in LDS; then each lane takes one
-//    (head dim, 8-position group) of the token-grouped page ([8][dh][8]),
-//    whose new positions are one contiguous run, and writes the run with
-//    the widest aligned stores that fit it (a full group is one 16-byte
-//    store for bf16).
+//  - values: stages token rows in LDS, two 8-position groups of the
+//    token-grouped page ([8][dh][8]) per pass and every row at its position's
+//    place in them; then, one group after the other, each lane takes a head dim
+//    and writes its run of new positions with the widest aligned stores that
+//    fit (a full group is one 16-byte store for bf16). The run of a group is
+//    the same in every lane, so the choice of stores is a scalar branch, and no
+//    group is written in two pieces.
+// Commits of few tokens are bound by the dispatch of the waves and their round
+// trips, wide ones by memory. Against staging 16 tokens from the first new
+// position with workgroup barriers and per-lane runs: 32 + 32 planes x 4 layers
+// x 55 heads x 1, 7, 30 and 64 tokens 10.6, 14.8, 45.4, 80.6 -> 9.6, 14.7,
+// 41.8, 70.5 us (265 MB, 3.8 TB/s). Measured and not kept: two or four units
+// per wave (17 and 22 us at 7 tokens), two head dims per lane (16 us: twice the
+// partial lines per store).
 // Pure copies: results are bit-exact.
 
 #include "das_internal.h"
@@ -22,57 +29,49 @@ namespace das {
 namespace {
 
 constexpr int kWaves = 4;
-constexpr int kChunk = 16;  // V tokens staged per pass
+constexpr int kRows = 16;  // value rows staged per pass: two groups
 
 struct alignas(16) Vec16 {
   uint32_t x, y, z, w;
 };
 
-// 32-bit words of elements (two bf16 per word, one fp32 per word).
-__device__ __forceinline__ uint32_t word(const bf16_t (&v)[8], int i) {
-  return static_cast<uint32_t>(v[2 * i]) | (static_cast<uint32_t>(v[2 * i + 1]) << 16);
-}
-__device__ __forceinline__ uint32_t word(const float (&v)[8], int i) {
-  return __float_as_uint(v[i]);
-}
-
 // Elements [lo, hi) of an 8-element row (16-byte aligned for bf16, 32 for
-// fp32) from v[], in aligned pieces of at most 16 bytes. Every piece position
-// is a compile-time constant, so v[] stays in registers.
-template <typename T>
-__device__ __forceinline__ void store_run(T *row, const T (&v)[8], int lo, int hi) {
-  constexpr int EPW = 4 / sizeof(T);  // elements per 32-bit word
+// fp32) from the row's words (two bf16 per word, one fp32), in aligned pieces
+// of at most 16 bytes.
+template <typename T, int NW>
+__device__ __forceinline__ void store_run(T *row, const uint32_t (&v)[NW], int lo, int hi) {
+  static_assert(NW * 4 == 8 * static_cast<int>(sizeof(T)), "eight elements");
   auto inside = [&](int a, int b) { return lo <= a && b <= hi; };
+  uint32_t *words = reinterpret_cast<uint32_t *>(row);
   if constexpr (sizeof(T) == 2) {
     if (inside(0, 8)) {
-      *reinterpret_cast<Vec16 *>(row) = Vec16{word(v, 0), word(v, 1), word(v, 2), word(v, 3)};
+      *reinterpret_cast<Vec16 *>(words) = Vec16{v[0], v[1], v[2], v[3]};
       return;
     }
   }
 #pragma unroll
   for (int q = 0; q < 8; q += 4) {
+    constexpr int HW = NW / 2;  // words of four elements
+    const int w0 = q / 4 * HW;
     if (inside(q, q + 4)) {  // 8 bytes (bf16) or 16 bytes (fp32)
-      const int w0 = q / EPW;
-      if constexpr (sizeof(T) == 2) {
-        *reinterpret_cast<uint2 *>(row + q) = make_uint2(word(v, w0), word(v, w0 + 1));
-      } else {
-        *reinterpret_cast<Vec16 *>(row + q) =
-            Vec16{word(v, w0), word(v, w0 + 1), word(v, w0 + 2), word(v, w0 + 3)};
-      }
+      if constexpr (sizeof(T) == 2)
+        *reinterpret_cast<uint2 *>(words + w0) = make_uint2(v[w0], v[w0 + 1]);
+      else
+        *reinterpret_cast<Vec16 *>(words + w0) = Vec16{v[w0], v[w0 + 1], v[w0 + 2], v[w0 + 3]};
       continue;
     }
 #pragma unroll
-    for (int e = q; e < q + 4; e += 2) {
-      if (inside(e, e + 2)) {  // 4 bytes (bf16) or 8 bytes (fp32)
-        if constexpr (sizeof(T) == 2) {
-          *reinterpret_cast<uint32_t *>(row + e) = word(v, e / 2);
-        } else {
-          *reinterpret_cast<uint2 *>(row + e) = make_uint2(word(v, e), word(v, e + 1));
+    for (int e = q; e < q + 4; ++e) {
+      if constexpr (sizeof(T) == 2) {
+        if (e % 2 == 0 && inside(e, e + 2)) {
+          words[e / 2] = v[e / 2];
+          continue;
         }
-        continue;
+        if (e % 2 == 1 && inside(e - 1, e + 1)) continue;
+        if (inside(e, e + 1)) row[e] = static_cast<T>(v[e / 2] >> (16 * (e % 2)));
+      } else {
+        if (inside(e, e + 1)) words[e] = v[e];
       }
-      if (inside(e, e + 1)) row[e] = v[e];
-      if (inside(e + 1, e + 2)) row[e + 1] = v[e + 1];
     }
   }
 }
@@ -81,7 +80,7 @@ template <typename T, int DH>
 __global__ __launch_bounds__(64 * kWaves) void kv_append_kernel(AppendParams p) {
   constexpr int VEC = 16 / sizeof(T);  // elements per 16-byte vector
   constexpr int NV = DH / VEC;         // vectors per token row
-  __shared__ __attribute__((aligned(16))) T stage[kWaves][kChunk * DH];
+  __shared__ __attribute__((aligned(16))) T stage[kWaves][kRows * DH];
 
   const int b = blockIdx.y;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
@@ -90,7 +89,6 @@ __global__ __launch_bounds__(64 * kWaves) void kv_append_kernel(AppendParams p) 
   const int k_blocks = (k_units + kWaves - 1) / kWaves;
   const bool is_v = static_cast<int>(blockIdx.x) >= k_blocks;
   const int rel = (is_v ? blockIdx.x - k_blocks : blockIdx.x) * kWaves + wave;
-  const bool live = rel < (is_v ? v_units : k_units);
 
   const int S = p.prefix_len[b];
   const int n = p.num_new[b];
@@ -100,7 +98,8 @@ __global__ __launch_bounds__(64 * kWaves) void kv_append_kernel(AppendParams p) 
     if (bad) report_error(p.dev_error, DAS_DEVERR_COMMIT);
     if (p.len_out) p.len_out[b] = bad ? S : S + n;
   }
-  if (bad || n == 0) return;  // uniform over the workgroup
+  // uniform over the wave; no workgroup barrier below
+  if (bad || n == 0 || rel >= (is_v ? v_units : k_units)) return;
 
   // n <= 64 new positions span at most two pages
   const int32_t *table = p.block_table + static_cast<size_t>(b) * p.max_pages;
@@ -125,7 +124,6 @@ __global__ __launch_bounds__(64 * kWaves) void kv_append_kernel(AppendParams p) 
       ((static_cast<size_t>(plane) * p.layers + layer) * p.hkv + h) * p.num_pages * kPage * DH;
 
   if (!is_v) {
-    if (!live) return;  // key workgroups use no barrier
     const T *src = static_cast<const T *>(p.k_new) + src_off;
     T *dst = static_cast<T *>(p.k_pool) + dst_head;
     const int total = n * NV;
@@ -155,45 +153,45 @@ __global__ __launch_bounds__(64 * kWaves) void kv_append_kernel(AppendParams p) 
     return;
   }
 
-  // values: every wave of the workgroup, live or not, runs the same chunk
-  // loop and its barriers (n is uniform)
   const T *src = static_cast<const T *>(p.v_new) + src_off;
   T *dst = static_cast<T *>(p.v_pool) + dst_head;
-  T *st = stage[wave];
-  for (int t0 = 0; t0 < n; t0 += kChunk) {
-    const int tc = min(kChunk, n - t0);
-    if (live) {
-      for (int v = lane; v < tc * NV; v += 64) {
-        const int t = v / NV, c = (v % NV) * VEC;
-        *reinterpret_cast<Vec16 *>(st + t * DH + c) =
-            *reinterpret_cast<const Vec16 *>(src + (t0 + t) * src_stride + c);
-      }
+  T *st = stage[wave];  // row r: position gbase + r
+  for (int gbase = S & ~7; gbase < S + n; gbase += kRows) {
+    const int r0 = max(S - gbase, 0), r1 = min(S + n - gbase, kRows);
+    for (int v = lane; v < (r1 - r0) * NV; v += 64) {
+      const int r = r0 + v / NV, c = (v % NV) * VEC;
+      *reinterpret_cast<Vec16 *>(st + r * DH + c) =
+          *reinterpret_cast<const Vec16 *>(src + (gbase + r - S) * src_stride + c);
     }
-    __syncthreads();
-    if (live) {
-      // item (dim c, 8-position group gi): the chunk's positions in that group
-      // are one contiguous run of the page's [group][c][8] row, written with
-      // the widest aligned stores that fit it
-      const int p0 = S + t0, p1 = p0 + tc;
-      const int gbase = p0 & ~7;
-      const int ngroups = (p1 - gbase + 7) >> 3;
-      for (int item = lane; item < DH * ngroups; item += 64) {
-        const int c = item % DH, gp = gbase + 8 * (item / DH);
-        const int lo = max(gp, p0), hi = min(gp + 8, p1);
-        const bool second = gp / kPage != first_page;  // 8 | 64: a group lies in one page
-        if (!(second ? ok1 : ok0)) continue;
-        const size_t page = second ? pg1 : pg0;
-        T *row = dst + page * kPage * DH + ((gp % kPage) / 8 * DH + c) * 8;
-        T v[8];
+    // the wave's own LDS writes are read by its other lanes
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int t = min(max(gp + j - p0, 0), tc - 1);  // staged token index
-          v[j] = (gp + j >= lo && gp + j < hi) ? st[t * DH + c] : T(0);
+    for (int g = 0; g < kRows; g += 8) {
+      const int lo = max(r0 - g, 0), hi = min(r1 - g, 8), gp = gbase + g;
+      const bool second = gp / kPage != first_page;  // 8 | 64: a group lies in one page
+      if (lo >= hi || !(second ? ok1 : ok0)) continue;  // uniform
+      T *rows = dst + static_cast<size_t>(second ? pg1 : pg0) * kPage * DH + gp % kPage * DH;
+      for (int c = lane; c < DH; c += 64) {
+        T e[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) e[j] = st[(g + j) * DH + c];
+        uint32_t w[2 * sizeof(T)];
+        if constexpr (sizeof(T) == 2) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            w[k] = static_cast<uint32_t>(e[2 * k]) | (static_cast<uint32_t>(e[2 * k + 1]) << 16);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) w[j] = __float_as_uint(e[j]);
         }
-        store_run<T>(row, v, lo - gp, hi - gp);
+        store_run<T>(rows + c * 8, w, lo, hi);
       }
     }
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
 }
 
