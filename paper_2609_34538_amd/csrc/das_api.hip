@@ -139,6 +139,7 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
   plan->ws_rec_bytes = 0;
   const int maxp = b->max_pages_per_seq;
   int pps = o ? o->pages_per_split : 0;
+  int even_pps = 0;  // > pps: the same number of splits without a short last one
   if (pps == 0) {
     const long tile_rows = plan->path == DAS_PATH_MFMA ? (plan->rows <= 16 ? 16 : 32)
                                                       : valu_tile_rows(plan->rows);
@@ -158,6 +159,21 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
     if (want < least) want = least;
     if (want > 32) want = 32;
     pps = static_cast<int>(want);
+    // Row tiles that share a workgroup: one round of them fills the chip (two
+    // workgroups of four waves per CU, four of two). The division above rounds
+    // down and so adds splits; where those past the first round hold more than
+    // half a split's pages, the prefix and the block are cut into
+    // `splits` even ones instead: 8 heads x 30000 tokens x 128 rows, dh 128, 68
+    // -> 59 splits 51.5 -> 39.8 us; 55 heads x 4000 x 64 rows, dh 96, 22 -> 16
+    // splits 30.8 -> 25.3; but 4 x 8 x 16384 x 128 rows, whose 17th split is one
+    // page, 66.1 against 67.2. The workspace stays sized for the former count.
+    if (mfma && plan->rows > 32 && pps < 32) {
+      const long slots = (mfma_waves(plan->rows) == 4 ? 2 : 4) * kNumCUs;
+      const long nw = mfma_waves(plan->rows), n_rt = (plan->rows + 31) / 32;
+      const long wgs = units / n_rt * ((n_rt + nw - 1) / nw);  // of one split
+      if (2 * (maxp + 1 - slots / wgs * pps) > pps)
+        even_pps = static_cast<int>((maxp + splits) / splits);
+    }
   }
   // at most maxp + 1 pages: one split then holds any sequence and its block
   if (pps > maxp + 1) pps = maxp + 1;
@@ -189,6 +205,10 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
     plan->ws_o_bytes = static_cast<size_t>(units) * plan->nsplit * plan->piece_stride;
     plan->ws_ml_bytes = 0;
     plan->total = plan->ws_o_bytes;
+    if (even_pps > pps && even_pps <= 32) {
+      plan->pages_per_split = even_pps;
+      plan->nsplit = splits_of(maxp, even_pps);
+    }
     return DAS_OK;
   }
   const size_t per_split_rows =

@@ -225,3 +225,24 @@ def test_non_finite_cache_past_the_prefix_is_ignored(name, path):
     torch.cuda.synchronize()
     ref, _ = oracle_call(cd, 0, d, wl.depth_R, q, kb, vb, range(wl.batch))
     assert_close(out, ref, wl.dtype, f"{name} {path} with non-finite cache past the prefix")
+
+
+@pytest.mark.parametrize("lens,hkv,group,dh,w", [
+    ([4000, 64, 3999, 0, 1500], 11, 4, 96, 16), ([7000], 8, 8, 128, 32), ([6913], 8, 8, 64, 32),
+    ([300] * 3 + [0, 257], 50, 8, 64, 32)])
+def test_even_splits_of_wide_blocks(lens, hkv, group, dh, w):
+    """Blocks of more than 32 query rows whose library-chosen splits would
+    leave more than one round of workgroups take even splits: prefixes that
+    end inside, at the end of and before the last one."""
+    wl = dg.scaled(W[3], batch=len(lens), hq=hkv * group, hkv=hkv, dh=dh, layers=1,
+                   prefix=(0, max(lens)), draft_depths=(2,), draft_widths=(w,), verify_width=w,
+                   paged_random=True)
+    cd = dg.make_cache(wl, DEV, prefix_lens=lens)
+    cache, batch = wrap(cd)
+    q, kb, vb = dg.block_inputs(cd, w, 2, DEV)
+    lse = torch.empty((wl.batch, wl.hq, w), dtype=torch.float32, device=DEV)
+    out = das.attn_policy(cache, batch, 0, 2, wl.depth_R, q, kb, vb, lse=lse)
+    torch.cuda.synchronize()
+    ref, ref_lse = oracle_call(cd, 0, 2, wl.depth_R, q, kb, vb, range(wl.batch))
+    assert_close(out, ref, wl.dtype, f"even splits lens={lens} G={group} dh={dh}")
+    assert_lse_close(lse, ref_lse, f"even splits lens={lens} lse")
