@@ -375,11 +375,17 @@ __device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf
   f32x4 sacc[NQ][E];
   hook(0);
   // reduction step outermost: the accumulators are independent, so no MFMA
-  // waits for the one before it
+  // waits for the one before it. One fp32 row tile sums its logits in two
+  // chains, which keeps that true and halves a chain's roundings (two row tiles
+  // alternate already, and spill at head dim 128 with four chains).
+  constexpr bool TWO = sizeof(T) == 4 && NQ == 1;
+  f32x4 odd[NQ];  // the second chain
 #pragma unroll
-  for (int qt = 0; qt < NQ; ++qt)
+  for (int qt = 0; qt < NQ; ++qt) {
+    odd[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int e = 0; e < E; ++e) sacc[qt][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 #pragma unroll
   for (int ks = 0; ks < QK; ++ks) {
     if constexpr (sizeof(T) == 2) {
@@ -392,11 +398,14 @@ __device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int qt = 0; qt < NQ; ++qt)
-          sacc[qt][0] = mfma16x16x4(kf[ks][i], qf[qt][ks][i], sacc[qt][0]);
+        for (int qt = 0; qt < NQ; ++qt) {
+          f32x4 &acc = TWO && (i & 1) ? odd[qt] : sacc[qt][0];
+          acc = mfma16x16x4(kf[ks][i], qf[qt][ks][i], acc);
+        }
     }
   }
   hook(1);
+  if constexpr (TWO) sacc[0][0] += odd[0];
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) {
     // raw logits; masked ones are -inf. scale > 0, so the maximum of the
