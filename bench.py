@@ -49,15 +49,16 @@ HBM_PEAK_GBS = 8000.0
 # reads for a plain 1 GiB device copy; valid only for the kernel sources with
 # this digest and the library's default plan.
 TRAFFIC_SOURCES = ["paper_2609_34538_amd/csrc/attn_mfma.hip",
+                   "paper_2609_34538_amd/csrc/attn_chunk.hip",
                    "paper_2609_34538_amd/csrc/attn_balanced.hip",
                    "paper_2609_34538_amd/csrc/attn_combine.hip",
                    "paper_2609_34538_amd/csrc/mfma_tile.h",
                    "paper_2609_34538_amd/csrc/das_api.hip",
                    "paper_2609_34538_amd/csrc/das_internal.h"]
-MEASURED_TRAFFIC = {("das-wave-step-bf16", "8c10ff5ae1b54562"): 4_467_655_546,
-                    ("long-prefix-gqa-bf16", "8c10ff5ae1b54562"): 310_069_010,
-                    ("ragged-paged-bf16", "8c10ff5ae1b54562"): 834_019_002,
-                    ("single-seq-looped-bf16", "8c10ff5ae1b54562"): 47_022_823}
+MEASURED_TRAFFIC = {("das-wave-step-bf16", "04b4abc2d7f66ffb"): 4_467_675_320,
+                    ("long-prefix-gqa-bf16", "04b4abc2d7f66ffb"): 310_268_609,
+                    ("ragged-paged-bf16", "04b4abc2d7f66ffb"): 834_102_880,
+                    ("single-seq-looped-bf16", "04b4abc2d7f66ffb"): 46_994_996}
 
 
 def kernel_digest():
