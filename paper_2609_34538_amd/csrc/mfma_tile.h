@@ -360,7 +360,12 @@ struct State {
 // LANE_SUM: st.l holds this lane's share of its row's sum (alpha is the same
 // in a row's 4 lanes), which the caller reduces over the 4 lanes when it
 // writes the row; otherwise st.l holds the row's sum after every tile.
-template <typename T, int DH, int NQ, bool LANE_SUM = false, typename Hook>
+// TWO: on wherever its registers fit (two row tiles at head dim 128 spill in the
+// split grid). Error against 64 bits of one chain / two: 2 x 8 heads x 350-700
+// tokens x 28 rows, dh 96, 4.2e-7 / 2.7e-7; 8 heads x 4000 x 32 rows, dh 128,
+// 5.8e-7 / 3.1e-7 (15.6 / 15.8 us).
+template <typename T, int DH, int NQ, bool LANE_SUM = false,
+          bool TWO = sizeof(T) == 4 && (NQ == 1 || DH < 128), typename Hook>
 __device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf)[DH / 16],
                                              const u32x4 (&vf)[DH / 16],
                                              const u32x4 (&qf)[NQ][Geo<T, DH, NQ, 1>::QK],
@@ -375,10 +380,8 @@ __device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf
   f32x4 sacc[NQ][E];
   hook(0);
   // reduction step outermost: the accumulators are independent, so no MFMA
-  // waits for the one before it. One fp32 row tile sums its logits in two
-  // chains, which keeps that true and halves a chain's roundings (two row tiles
-  // alternate already, and spill at head dim 128 with four chains).
-  constexpr bool TWO = sizeof(T) == 4 && NQ == 1;
+  // waits for the one before it. TWO: fp32 logits in two chains, which keeps
+  // that true with one row tile and halves a chain's roundings.
   f32x4 odd[NQ];  // the second chain
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) {
@@ -405,7 +408,10 @@ __device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf
     }
   }
   hook(1);
-  if constexpr (TWO) sacc[0][0] += odd[0];
+  if constexpr (TWO) {
+#pragma unroll
+    for (int qt = 0; qt < NQ; ++qt) sacc[qt][0] += odd[qt];
+  }
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) {
     // raw logits; masked ones are -inf. scale > 0, so the maximum of the
