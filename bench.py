@@ -55,10 +55,9 @@ TRAFFIC_SOURCES = ["paper_2609_34538_amd/csrc/attn_mfma.hip",
                    "paper_2609_34538_amd/csrc/mfma_tile.h",
                    "paper_2609_34538_amd/csrc/das_api.hip",
                    "paper_2609_34538_amd/csrc/das_internal.h"]
-MEASURED_TRAFFIC = {("das-wave-step-bf16", "04b4abc2d7f66ffb"): 4_467_675_320,
-                    ("long-prefix-gqa-bf16", "04b4abc2d7f66ffb"): 310_268_609,
-                    ("ragged-paged-bf16", "04b4abc2d7f66ffb"): 834_102_880,
-                    ("single-seq-looped-bf16", "04b4abc2d7f66ffb"): 46_994_996}
+MEASURED_TRAFFIC = {("das-wave-step-bf16", "33679d349612bf4f"): 4_467_675_320,
+                    ("long-prefix-gqa-bf16", "33679d349612bf4f"): 310_268_609,
+                    ("ragged-paged-bf16", "33679d349612bf4f"): 834_102_880}
 
 
 def kernel_digest():

@@ -242,8 +242,8 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
 //   128, 32 rows 94 against 111). fp32 blocks of two row tiles are bound by
 //   the matrix cores and gain from two waves per SIMD: 16 x 55 heads x 512-4096
 //   x 32 rows 355 -> 328 us.
-// - against the split grid, blocks of one row tile: otherwise always (55 heads
-//   x 2000 tokens, dh 96, 13.6 -> 12.7 us; 45 x 22698, dh 128, 88 -> 78; 32
+// - against the split grid, blocks of one row tile: otherwise always but
+//   for the middle unit counts named below (45 x 22698, dh 128, 88 -> 78; 32
 //   heads x 1300 10.7 -> 8.9; 512 units x 1024-8192, dh 128, 20 rows, 239 ->
 //   200; fp32 512 units x 512-4096, dh 128, 32 rows 498 -> 261). Blocks of several row tiles read each tile once per row
 //   tile, from the L2 as long as they keep pace (18 tiles per wave; 55 heads x
@@ -308,6 +308,13 @@ void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes,
     }
   }
   if (!best_k) return;
+  // 24-80 units in several chunks each, up to the last-level cache's 256 MB: the
+  // two are even on repeated reads (four calls of 55 heads x 2048 tokens 52 us)
+  // but in a step that reads each prefix from memory chunks were slower, 151
+  // against 134 us (four draft and four verifier calls and the commit).
+  if (plan->path == DAS_PATH_MFMA && es == 2 && n_rt == 1 && best_ns > 1 && units >= 24 &&
+      units <= 80 && 2.f * tile_bytes * tiles * seq_heads < 256e6f)
+    return;
   if (plan->path == DAS_PATH_MFMA && es == 2 && n_rt > 1) {
     // the shared ring: launch, merge and the stream at 4.2 or 3 TB/s (the
     // lengths of a batch vary; chunks of a unit suffer less from that)
