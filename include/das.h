@@ -154,9 +154,7 @@ typedef enum das_attn_path {
   DAS_PATH_VALU = 1,     /* vector-ALU kernel (on fp32 caches the only path that
                             can be asked for; DAS_PATH_AUTO runs most fp32
                             requests on the matrix cores, in full fp32)      */
-  DAS_PATH_MFMA = 2,     /* matrix-core kernels over prefix splits, or with
-                            pages_per_split 0 over chunks of tiles where the
-                            library finds them faster (bf16)                 */
+  DAS_PATH_MFMA = 2,     /* matrix-core kernel over prefix splits (bf16)     */
   DAS_PATH_BALANCED = 3  /* matrix-core kernel, persistent balanced schedule:
                             every resident wave streams an equal share of
                             all sequences' tiles (bf16, 1..64 sequences,

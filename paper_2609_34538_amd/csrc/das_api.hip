@@ -342,10 +342,9 @@ das_status make_plan(const das_cache *c, const das_batch *b, int hq, int w,
   plan->rows = w * group;
   plan->chunk_tiles = 0;
   const int path = choose_path(c, b, plan->rows, o);
-  // where the caller leaves the kernel, or the cut of the matrix-core grid, to
-  // the library
-  const bool may_chunk = !o || ((o->path == DAS_PATH_AUTO || o->path == DAS_PATH_MFMA) &&
-                                o->pages_per_split == 0);
+  // where the caller leaves the kernel and its cut to the library; a call that
+  // names a path runs that path's kernel
+  const bool may_chunk = !o || (o->path == DAS_PATH_AUTO && o->pages_per_split == 0);
   if (c->dtype != DAS_F32 || path == DAS_PATH_VALU) {
     const das_status st = plan_path(c, b, w, o, path, plan);
     if (st == DAS_OK && may_chunk) plan_chunks(c, b, w, ws_bytes, plan);

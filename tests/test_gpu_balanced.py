@@ -91,8 +91,8 @@ def test_all_prefixes_empty():
 def test_library_choice_and_determinism():
     """The library takes the balanced schedule for a batch of 2..64 sequences
     with more than W / 8 (sequence, KV head) units (bit-identical to asking
-    for it), the split grid for fewer units or when a split size is given;
-    repeated calls agree bit for bit."""
+    for it), another kernel for fewer units, the split grid when a split size
+    is given; repeated calls agree bit for bit."""
     lens = [1500, 333, 4096, 0, 2047]
     # 5 x 40 = 200 units > 1280 / 8 at head dim 96
     wl, cd, (cache, batch, q, kb, vb), out, _ = _run(lens, 40, 40, 96, 16)
@@ -105,14 +105,18 @@ def test_library_choice_and_determinism():
     assert torch.equal(auto.view(torch.int16), out.view(torch.int16))
     assert torch.equal(again.view(torch.int16), out.view(torch.int16))
     assert torch.equal(grid.view(torch.int16), grid_ref.view(torch.int16))
-    # 5 x 4 = 20 units: the split grid with the library's split size
+    # 5 x 4 = 20 units: not the balanced schedule; asking for the matrix-core
+    # path runs the split grid, of 4 pages a split unless told otherwise
     wl, cd, (cache, batch, q, kb, vb), bal, _ = _run(lens, 4, 4, 96, 16)
     auto = das.attn_policy(cache, batch, 0, 2, wl.depth_R, q, kb, vb)
     grid = das.attn_policy(cache, batch, 0, 2, wl.depth_R, q, kb, vb, path="mfma")
+    grid_4 = das.attn_policy(cache, batch, 0, 2, wl.depth_R, q, kb, vb, path="mfma",
+                             pages_per_split=4)
     torch.cuda.synchronize()
-    assert torch.equal(auto.view(torch.int16), grid.view(torch.int16))
+    assert torch.equal(grid.view(torch.int16), grid_4.view(torch.int16))
     ref, _ = oracle_call(cd, 0, 2, wl.depth_R, q, kb, vb, range(wl.batch))
     assert_close(auto, ref, wl.dtype, "library choice, few units")
+    assert_close(grid, ref, wl.dtype, "split grid, few units")
     assert_close(bal, ref, wl.dtype, "balanced, few units")
 
 
