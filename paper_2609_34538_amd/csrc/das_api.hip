@@ -139,7 +139,7 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
   plan->ws_rec_bytes = 0;
   const int maxp = b->max_pages_per_seq;
   int pps = o ? o->pages_per_split : 0;
-  int even_pps = 0;  // > pps: the same number of splits without a short last one
+  int even_pps = 0;  // > pps: fewer splits, of equal length
   if (pps == 0) {
     const long tile_rows = plan->path == DAS_PATH_MFMA ? (plan->rows <= 16 ? 16 : 32)
                                                       : valu_tile_rows(plan->rows);
@@ -159,20 +159,33 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
     if (want < least) want = least;
     if (want > 32) want = 32;
     pps = static_cast<int>(want);
-    // Row tiles that share a workgroup: one round of them fills the chip (two
-    // workgroups of four waves per CU, four of two). The division above rounds
-    // down and so adds splits; where those past the first round hold more than
-    // half a split's pages, the prefix and the block are cut into
-    // `splits` even ones instead: 8 heads x 30000 tokens x 128 rows, dh 128, 68
-    // -> 59 splits 51.5 -> 39.8 us; 55 heads x 4000 x 64 rows, dh 96, 22 -> 16
-    // splits 30.8 -> 25.3; but 4 x 8 x 16384 x 128 rows, whose 17th split is one
-    // page, 66.1 against 67.2. The workspace stays sized for the former count.
+    // Row tiles that share a workgroup: the division above rounds down and so
+    // adds one short split or more to the planned ones. The prefix and the block
+    // are cut into `splits` even ones instead, with the longer splits,
+    // - for two row tiles of bf16 where they are more than three workgroups per
+    //   CU, which then get three or four each (even ones three, or less and
+    //   alike): 96 heads x 12000 tokens x 64 rows, dh 64, 9 -> 8 splits 68.7 ->
+    //   59.9 us; 55 heads x 4000, dh 96, 22 -> 16 splits 30.8 -> 25.3; but 40
+    //   heads x 8000 x 48 rows, dh 64, 19 splits 23.9 against 25.6 with 16. 776
+    //   shapes of 24-256 units x 1000-16000 tokens 1.03-1.06x, at worst 0.95;
+    // - for four waves, and for fp32, which a short split costs less than a
+    //   longer one, where those past the first round of workgroups (two of four
+    //   waves per CU, four of two) hold more than half a split's pages and the
+    //   even ones exceed that round by a fifth at most: 8 heads x 30000 tokens x
+    //   128 rows, dh 128, 68 -> 59 splits 51.5 -> 39.8 us; but not 4 x 8 x 16384
+    //   x 128 rows, whose 17th split is one page (66.1 against 67.2), and not 40
+    //   heads x 8000 x 72 rows (three row tiles: 640 even workgroups), dh 96, 43.1
+    //   against 46.1; fp32 96 heads x 8000 x 64 rows, dh 96, 218 against 229.
+    // The workspace stays sized for the former count.
     if (mfma && plan->rows > 32 && pps < 32) {
-      const long slots = (mfma_waves(plan->rows) == 4 ? 2 : 4) * kNumCUs;
       const long nw = mfma_waves(plan->rows), n_rt = (plan->rows + 31) / 32;
       const long wgs = units / n_rt * ((n_rt + nw - 1) / nw);  // of one split
-      if (2 * (maxp + 1 - slots / wgs * pps) > pps)
-        even_pps = static_cast<int>((maxp + splits) / splits);
+      const long round = (nw == 4 ? 2 : 4) * kNumCUs;
+      const int even = static_cast<int>((maxp + splits) / splits);
+      const bool uneven = nw == 2 && es == 2 && splits_of(maxp, pps) * wgs > 3 * kNumCUs;
+      if (uneven || (2 * (maxp + 1 - round / wgs * pps) > pps &&
+                     5 * splits_of(maxp, even) * wgs <= 6 * round))
+        even_pps = even;
     }
   }
   // at most maxp + 1 pages: one split then holds any sequence and its block

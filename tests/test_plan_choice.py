@@ -43,3 +43,21 @@ def test_default_splits_of_the_split_grid():
                                      ((1, 8, 1, 20, 8), 11), ((32, 8, 1, 1000, 8), 32)):
         p = plan("bf16", b, hkv, g, 128, pages, w, path="mfma")
         assert p.nsplit == n, (b, hkv, g, pages, w, p)
+
+
+@pytest.mark.parametrize("dtype,hkv,group,dh,pages,w,nsplit,pps", [
+    # two row tiles: even splits where the rounded-down ones pass three workgroups
+    # per CU
+    ("bf16", 96, 1, 64, 188, 64, 8, 24), ("bf16", 128, 1, 64, 126, 48, 8, 16),
+    ("bf16", 55, 1, 96, 63, 64, 16, 4), ("bf16", 40, 1, 64, 126, 48, 19, 7),
+    # four waves: past the first round, but not with three row tiles, whose even
+    # splits need a second round as well, nor for a last split of one page
+    ("bf16", 8, 4, 128, 469, 32, 59, 8), ("bf16", 40, 8, 96, 126, 9, 19, 7),
+    ("bf16", 32, 4, 128, 257, 32, 17, 16),
+    # fp32: past the first round only
+    ("f32", 96, 1, 96, 126, 64, 9, 15), ("f32", 64, 1, 96, 188, 64, 16, 12)])
+def test_even_splits(dtype, hkv, group, dh, pages, w, nsplit, pps):
+    path = "mfma" if dtype == "bf16" else "auto"
+    p = plan(dtype, 1, hkv, group, dh, pages, w, path=path)
+    assert p.kernel == "split" and (p.nsplit, p.pages_per_split) == (nsplit, pps), p
+    assert p.nsplit * p.pages_per_split >= pages + 1
