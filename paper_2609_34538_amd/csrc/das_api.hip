@@ -171,11 +171,13 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
     // - for four waves, and for fp32, which a short split costs less than a
     //   longer one, where those past the first round of workgroups (two of four
     //   waves per CU, four of two) hold more than half a split's pages and the
-    //   even ones exceed that round by a fifth at most: 8 heads x 30000 tokens x
-    //   128 rows, dh 128, 68 -> 59 splits 51.5 -> 39.8 us; but not 4 x 8 x 16384
-    //   x 128 rows, whose 17th split is one page (66.1 against 67.2), and not 40
-    //   heads x 8000 x 72 rows (three row tiles: 640 even workgroups), dh 96, 43.1
-    //   against 46.1; fp32 96 heads x 8000 x 64 rows, dh 96, 218 against 229.
+    //   even ones' rounds take no more pages in turn (a twentieth aside): 8 heads x
+    //   30000 tokens x 128 rows, dh 128, 68 -> 59 splits 51.5 -> 39.8 us; 18 x 55
+    //   heads x 152-319 x 232 rows, dh 64, 3 -> 2 splits 114 -> 94; but not 4 x 8
+    //   x 16384 x 128 rows, whose 17th split is one page (66.1 against 67.2), and
+    //   not 40 heads x 8000 x 72 rows (three row tiles: 640 even workgroups are two
+    //   rounds), dh 96, 43.1 against 46.1; fp32 96 heads x 8000 x 64 rows, dh 96, 218
+    //   against 229.
     // The workspace stays sized for the former count.
     if (mfma && plan->rows > 32 && pps < 32) {
       const long nw = mfma_waves(plan->rows), n_rt = (plan->rows + 31) / 32;
@@ -183,8 +185,10 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
       const long round = (nw == 4 ? 2 : 4) * kNumCUs;
       const int even = static_cast<int>((maxp + splits) / splits);
       const bool uneven = nw == 2 && es == 2 && splits_of(maxp, pps) * wgs > 3 * kNumCUs;
+      // pages that the rounds of workgroups take one after the other
+      auto pages = [&](int p) { return (splits_of(maxp, p) * wgs + round - 1) / round * p; };
       if (uneven || (2 * (maxp + 1 - round / wgs * pps) > pps &&
-                     5 * splits_of(maxp, even) * wgs <= 6 * round))
+                     20 * pages(even) <= 21 * pages(pps)))
         even_pps = even;
     }
   }

@@ -50,10 +50,12 @@ def test_default_splits_of_the_split_grid():
     # per CU
     ("bf16", 96, 1, 64, 188, 64, 8, 24), ("bf16", 128, 1, 64, 126, 48, 8, 16),
     ("bf16", 55, 1, 96, 63, 64, 16, 4), ("bf16", 40, 1, 64, 126, 48, 19, 7),
-    # four waves: past the first round, but not with three row tiles, whose even
-    # splits need a second round as well, nor for a last split of one page
+    # four waves: past the first round, where the even ones' rounds take no more
+    # pages in turn (not with three row tiles, which need a second round as
+    # well), and not for a last split of one page
     ("bf16", 8, 4, 128, 469, 32, 59, 8), ("bf16", 40, 8, 96, 126, 9, 19, 7),
-    ("bf16", 32, 4, 128, 257, 32, 17, 16),
+    ("bf16", 32, 4, 128, 257, 32, 17, 16), ("bf16", 990, 4, 64, 5, 58, 2, 3),
+    ("bf16", 25, 4, 96, 328, 34, 16, 21),
     # fp32: past the first round only
     ("f32", 96, 1, 96, 126, 64, 9, 15), ("f32", 64, 1, 96, 188, 64, 16, 12)])
 def test_even_splits(dtype, hkv, group, dh, pages, w, nsplit, pps):
