@@ -243,13 +243,20 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
 // wave. Chosen where it measured faster than the plan it replaces (uniform and
 // ragged batches of 1-48 sequences, 4-2000 units, 24-30000 tokens, both types,
 // every head dim, 1-512 rows):
-// - one chunk per unit needs no merge (5.2 us and the record traffic), but a
-//   CU takes no more than about 50 GB/s from memory, so long units need
-//   several; with k > 1 a wave waits for every tile in turn (0.75 us and its
-//   arithmetic). The estimate below, in us per call and without the launch,
-//   weighs these, the whole stream at 6.3 TB/s (lengths averaging 0.6 of the
-//   table's) and the dispatch of many workgroups. Single short sequence (55
-//   heads, 331 tokens): 8.9 -> 6.8 us; 4 x 55 heads x 512-2048: 33.5 -> 19.4.
+// - one chunk per unit needs no merge (3.9 us and the record traffic), but a
+//   CU takes no more than about 38 GB/s from a large pool in memory (50 of a
+//   batch's table width, which its lengths do not fill), so long units need several; with k > 1 a
+//   wave waits for every tile in turn (1 us and its arithmetic). The estimate
+//   below, in us per call and without the launch, weighs these, the whole
+//   stream (8.5 TB/s of the table's width: memory gives 6.3, a batch's lengths
+//   average less than its table, and between plans that are all bound by it the
+//   others decide) and the dispatch of many workgroups. Its constants are fitted
+//   to every cut of 3186 calls (8-256 units x 160-16000 tokens, every head dim, 8
+//   and 32 rows, one sequence and four ragged ones, pages spread over 48 GB and
+//   cached): the cut it takes is 1.3-1.4 % off the best one on average, and
+//   against the split grid in its first form 0.92 at worst (46 calls below 0.97).
+//   Single short sequence (55 heads, 331 tokens): 8.9 -> 6.8 us; 4 x 55 heads x
+//   512-2048: 33.5 -> 19.4.
 // - against the balanced schedule, which does not care how unequal the lengths
 //   are: units of up to 1.6 MB (4 x 55 heads x 512-4096 tokens 53.5 -> 47 us,
 //   but 1024-8192 tokens 51 against 61), and, when they do not all fit at once,
@@ -259,16 +266,18 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
 //   128, 32 rows 94 against 111). fp32 blocks of two row tiles are bound by
 //   the matrix cores and gain from two waves per SIMD: 16 x 55 heads x 512-4096
 //   x 32 rows 355 -> 328 us.
-// - against the split grid, blocks of one row tile: otherwise always but
-//   for the middle unit counts named below (45 x 22698, dh 128, 88 -> 78; 32
-//   heads x 1300 10.7 -> 8.9; 512 units x 1024-8192, dh 128, 20 rows, 239 ->
-//   200; fp32 512 units x 512-4096, dh 128, 32 rows 498 -> 261). Blocks of several row tiles read each tile once per row
-//   tile, from the L2 as long as they keep pace (18 tiles per wave; 55 heads x
-//   9000 tokens, 36 per wave, 52 against 65 us): at most one workgroup per CU
-//   where a unit has several chunks, and only where
-//   the estimate beats the shared ring's: 16 x 8 heads x 1000 tokens x 52 rows,
-//   dh 128, 28.6 -> 17.9 us, x 512-8192 tokens 61 against 97; 4 x 8 heads x
-//   300 tokens x 100 rows 12.7 -> 9.8, x 2500 20-25 us either way.
+// - against the split grid, blocks of one row tile: otherwise always, but for
+//   several chunks where that grid fills the chip (below): 80 heads x 4000, dh 64,
+//   26.0 -> 20.8 us; 512 units x 1024-8192, dh 128, 20 rows, 239 -> 200; fp32 512
+//   units x 512-4096, dh 128, 32 rows 498 -> 261. Blocks of several row tiles read
+//   each tile once per row tile, from the L2 as long as they keep pace (18 tiles
+//   per wave; 55 heads x 9000 tokens, 36 per wave, 52 against 65 us): at most one
+//   workgroup per CU where a unit has several chunks, and, in bf16, only where
+//   the estimate beats the shared ring's: 16 x 8 heads x 1000 tokens x 52 rows, dh
+//   128, 28.6 -> 17.9 us, x 512-8192 tokens 61 against 97; 4 x 8 heads x 300
+//   tokens x 100 rows 12.7 -> 9.8, x 2500 20-25 us either way. fp32 always: 1.15
+//   to 1.19 times the shared ring's rate on average over 813 shapes, though not at
+//   every one (24 heads x 6000 tokens x 128 rows, dh 64, 87 against 65 us).
 // - in place of the vector-ALU kernel (narrow fp32 blocks over few tiles):
 //   always.
 void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes, Plan *plan) {
@@ -279,7 +288,7 @@ void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes,
   if (seq_heads > 65536 || all_tiles > 65536) return;
   const int n_rt = (plan->rows + 16 * nq - 1) / (16 * nq);
   const int units = static_cast<int>(seq_heads) * n_rt, tiles = static_cast<int>(all_tiles);
-  const float tile_bytes = 128.f * c->head_dim;  // keys; the values are as many
+  const float tile_bytes = 128.f * c->head_dim;  // keys and values, 64 * dh each
   const int whole_k = (tiles + kChunkWaves - 1) / kChunkWaves;  // tiles of a wave, one chunk per unit
   const int rounds = (units + kNumCUs - 1) / kNumCUs;
   const bool f32_wide = es == 4 && nq == 2;
@@ -290,20 +299,20 @@ void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes,
       tiles * tile_bytes * rounds * kNumCUs > 450e6f)
     return;
 
-  const float t_mem = kChunkWaves * tile_bytes / 50e3f;
-  const float t_cmp = nq * c->head_dim * (es == 4 ? 16.f / 2400.f : 0.27f / 100.f);
-  const float t_hbm = static_cast<float>(seq_heads) * tiles * tile_bytes / 10e6f;
+  const float t_mem = kChunkWaves * tile_bytes / (b->batch == 1 || es == 4 ? 38e3f : 50e3f);
+  const float t_cmp = nq * c->head_dim * (es == 4 ? 16.f / 2400.f : 0.002f);
+  const float t_hbm = static_cast<float>(seq_heads) * tiles * tile_bytes / 8.5e6f;
   const float t_wg = nq == 2 ? 0.0115f : 0.0065f;
   const size_t stride = piece_record_bytes(plan->rows, c->head_dim, es);
   auto time = [&](int k, int ns) {
     const int m = (units * ns + kNumCUs - 1) / kNumCUs;
-    float t = k * (0.75f + t_cmp);
+    float t = k * (1.f + t_cmp);
     if (m * k * t_cmp > t) t = m * k * t_cmp;
     if (m * k * t_mem > t) t = m * k * t_mem;
     if (n_rt > 1) t *= 1.1f;
     if (t_hbm > t) t = t_hbm;
     if (units * ns * t_wg > t) t = units * ns * t_wg;
-    if (ns > 1) t += 5.2f + 0.02f * ns + static_cast<float>(stride * ns * seq_heads) / 1.5e6f;
+    if (ns > 1) t += 3.9f + 0.012f * ns + static_cast<float>(stride * ns * seq_heads) / 0.88e6f;
     return t;
   };
   // bf16 requests keep the workspace they always asked for; fp32 ones may take
@@ -325,18 +334,37 @@ void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes,
     }
   }
   if (!best_k) return;
-  // 24-80 units in several chunks each, up to the last-level cache's 256 MB: the
-  // two are even on repeated reads (four calls of 55 heads x 2048 tokens 52 us)
-  // but in a step that reads each prefix from memory chunks were slower, 151
-  // against 134 us (four draft and four verifier calls and the commit).
-  if (plan->path == DAS_PATH_MFMA && es == 2 && n_rt == 1 && best_ns > 1 && units >= 24 &&
-      units <= 80 && 2.f * tile_bytes * tiles * seq_heads < 256e6f)
+  // Tables of one page, two row tiles, more units than two per CU: the split grid
+  // needs no merge either, and one wave for the three tiles at most: dh 128, 31
+  // rows, 440 units 12.1 / 10.6, 880 17.1 / 20.1, 1760 31.4 / 34.7, 3520 53.5 /
+  // 60.7 us (split / chunk).
+  if (plan->path == DAS_PATH_MFMA && es == 2 && n_rt == 1 && nq == 2 && plan->nsplit == 1 &&
+      units > 2 * kNumCUs)
     return;
+  // Several chunks of several tiles per wave, 16 units and more: only where the
+  // split grid's power of two of splits leaves over 30 % of its 512 waves idle.
+  // Elsewhere the two are within a few percent in calls on their own (55 heads x
+  // 2048 tokens from memory 13.6 split, 13.8 chunks; 64 x 2000 14.9, 14.4), but a
+  // step that commits to many planes is slower with chunks: their key loads
+  // displace the written lines from the last-level cache, where the split grid's
+  // are non-temporal. Four layers of draft, verifier and the commit to 32 + 32
+  // planes, dh 96, split / chunks: 16 units x 2048 80 / 86 us, 24 x 4096 107 / 121,
+  // 55 x 2048 121 / 141, 128 x 2048 195 / 228; 8 x 2048 74 / 67, 8 x 8192 101 /
+  // 100. Idle waves: 40 units x 4096, dh 64, 143 / 131, dh 96 154 / 160; the same
+  // in four sequences with a commit to 6 planes 148 / 125.
+  if (plan->path == DAS_PATH_MFMA && es == 2 && n_rt == 1 && best_ns > 1 && best_k > 1 &&
+      units >= 16) {
+    int splits = 2;
+    while (splits * 2 * units <= 512) splits *= 2;
+    if (10 * splits * units > 7 * 512) return;
+  }
   if (plan->path == DAS_PATH_MFMA && es == 2 && n_rt > 1) {
     // the shared ring: launch, merge and the stream at 4.2 or 3 TB/s (the
     // lengths of a batch vary; chunks of a unit suffer less from that)
-    const float slope = b->batch == 1 ? 2.4f : best_ns > 1 ? 1.9f : 1.45f;
-    if (best_k > 18 || best + 3.f > (n_rt == 2 ? 8.5f + slope * t_hbm : 9.5f + 1.38f * slope * t_hbm)) return;
+    const float slope = b->batch == 1 ? 2.04f : best_ns > 1 ? 1.6f : 1.23f;
+    if (best_k > 18 ||
+        best > (n_rt == 2 ? 6.f + slope * t_hbm : 9.5f + 1.38f * slope * t_hbm))
+      return;
   }
   plan->chunk_tiles = kChunkWaves * best_k;
   plan->nsplit = best_ns;

@@ -63,3 +63,41 @@ def test_even_splits(dtype, hkv, group, dh, pages, w, nsplit, pps):
     p = plan(dtype, 1, hkv, group, dh, pages, w, path=path)
     assert p.kernel == "split" and (p.nsplit, p.pages_per_split) == (nsplit, pps), p
     assert p.nsplit * p.pages_per_split >= pages + 1
+
+
+@pytest.mark.parametrize("hkv,dh,pages,w,kernel,nsplit", [
+    # one chunk per unit at any unit count
+    (55, 96, 6, 1, "chunk", 1), (55, 96, 8, 8, "chunk", 1), (180, 96, 33, 8, "chunk", 1),
+    # several of one tile per wave
+    (24, 96, 17, 8, "chunk", 9),
+    # several of more: below 16 units
+    (15, 96, 129, 8, "chunk", 17), (16, 96, 129, 8, "split", 33),
+    # from there where the power of two of splits leaves over 30 % of 512 waves idle
+    (40, 96, 33, 8, "chunk", 6), (44, 96, 33, 8, "chunk", 5), (45, 96, 33, 8, "split", 9),
+    (55, 96, 33, 8, "split", 9), (80, 96, 33, 8, "chunk", 3), (89, 96, 129, 8, "chunk", 5),
+    (90, 96, 129, 8, "split", 5), (128, 96, 33, 8, "split", 5), (64, 64, 129, 17, "split", 9),
+    (160, 96, 33, 8, "chunk", 3),
+    # tables of one page and two row tiles
+    (512, 128, 1, 31, "chunk", 1), (513, 128, 1, 31, "split", 1), (513, 128, 2, 31, "chunk", 1),
+    (513, 128, 1, 16, "chunk", 1)])
+def test_chunks_against_the_split_grid(hkv, dh, pages, w, kernel, nsplit):
+    p = plan("bf16", 1, hkv, 1, dh, pages, w)
+    assert (p.kernel, p.nsplit) == (kernel, nsplit), p
+
+
+def test_any_workspace_that_was_enough_stays_enough():
+    """A call's own workspace size is accepted; fp32 calls also run in the
+    vector-ALU plan's, and in the library's scratch wherever either fits."""
+    for dtype, b, hkv, g, dh, pages, w in _shapes(600, 2):
+        p = plan(dtype, b, hkv, g, dh, pages, w)
+        if p.workspace == 0:
+            assert p.status < 0
+            continue
+        assert p.status == 0, p
+        assert plan(dtype, b, hkv, g, dh, pages, w, workspace=p.workspace + 4096).status == 0
+        fits = p.workspace <= 64 << 20
+        if dtype == "f32":
+            valu = plan(dtype, b, hkv, g, dh, pages, w, path="valu")
+            assert plan(dtype, b, hkv, g, dh, pages, w, workspace=valu.workspace).status == 0
+            fits = fits or valu.workspace <= 64 << 20
+        assert (plan(dtype, b, hkv, g, dh, pages, w, noalloc=True).status == 0) == fits
