@@ -138,6 +138,8 @@ void attn_balanced_kernel(AttnParams p) {
   constexpr int ES = G::ES;
   constexpr int TT = G::TT;
   constexpr int TPP = G::TPP;
+  constexpr int kPageShift = TPP == 4 ? 2 : 1;  // tile -> page of the unit
+  static_assert(TPP == 1 << kPageShift, "tiles per page");
   constexpr int QK = G::QK;
   constexpr int KS = G::KS;
   constexpr int DT = G::DT;
@@ -218,14 +220,16 @@ void attn_balanced_kernel(AttnParams p) {
     if (!ok) report_error(p.dev_error, DAS_DEVERR_PAGE);
     const size_t off = (static_cast<size_t>(x.kvh) * p.num_pages + (ok ? page : 0)) *
                        kPage * DH * ES;
-    const int u = x.t % TPP;
+    const int u = x.t & (TPP - 1);
     kbase = kl + off + 64 * DH * u;
     vbase = vl + off + 64 * DH * u;
   };
-  // Key load f of a tile (see the split-grid kernel).
+  // Key load f of a tile (see the split-grid kernel). Only the whole-line loads
+  // have offsets worth making anew, and page numbers are shifts: bf16 at head dim
+  // 128 had lost 0.5-1 % to these (800 units x 932 tokens 77.3 -> 76.7 us).
   auto load_key = [&](__amdgpu_buffer_rsrc_t r, int f, uint8_t *slot) {
     uint32_t base = load_k[f % G::LP];
-    if (DH == 128) asm volatile("" : "+v"(base));
+    if (sizeof(T) == 4 && DH == 128) asm volatile("" : "+v"(base));
     dma16<kNonTemporal>(r, base ^ G::key_load_xor(f), G::key_load_off(f), slot + f * kFragBytes);
   };
   // Loads of a tile into ring slot `si`, in three parts (key fragments of
@@ -338,7 +342,7 @@ void attn_balanced_kernel(AttnParams p) {
   // loaded one window or one unit ahead; the wait at the top of every tile
   // completes them with the tile.
   Cursor cu = c0;
-  int pw0 = (c0.t / TPP) & ~63;
+  int pw0 = (c0.t >> kPageShift) & ~63;
   int pwin = load_window(cu.b, pw0);
   int x_pw0 = -1;  // first page of the prefetched next window (-1: none)
   int pwin_x = 0;
@@ -356,7 +360,7 @@ void attn_balanced_kernel(AttnParams p) {
   const char *kbase, *vbase;
   bool ok_cur;
   {
-    const int pg = cu.t / TPP;
+    const int pg = cu.t >> kPageShift;
     tile_src(cu, __builtin_amdgcn_readlane(pwin, pg - pw0), kbase, vbase, ok_cur);
     for (int part = 0; part < 3; ++part) issue_part(0, cu, part, kbase, vbase);
   }
@@ -431,7 +435,7 @@ void attn_balanced_kernel(AttnParams p) {
       if (refill) {
         int page = 0;
         if (ci.t < TPP * ci.np) {
-          const int pg = ci.t / TPP;
+          const int pg = ci.t >> kPageShift;
           if (!in_unit) {
             page = __builtin_amdgcn_readlane(pwin_n, pg);
           } else {
