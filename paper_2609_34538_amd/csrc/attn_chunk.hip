@@ -173,7 +173,7 @@ void attn_chunk_kernel(AttnParams p, int n_rt) {
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
       vf[dt] = gather_block_values<T, DH>(reinterpret_cast<const uint8_t *>(part[wave]), dt, ln, lg);
-    compute_tile<T, DH, NQ, true, ES == 4>(st, kf, vf, qf, cap, p.w - TT * wave, false, p.scale_log2, lg,
+    compute_tile<T, DH, NQ, true>(st, kf, vf, qf, cap, p.w - TT * wave, false, p.scale_log2, lg,
                                   [&](int stage) {
                                     if (stage == 1 && n > 1) load_keys(1);
                                   });
@@ -195,7 +195,7 @@ void attn_chunk_kernel(AttnParams p, int n_rt) {
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) vf[dt] &= keep;
     }
-    compute_tile<T, DH, NQ, true, ES == 4>(st, kf, vf, qf, cap, limit, full, p.scale_log2, lg,
+    compute_tile<T, DH, NQ, true>(st, kf, vf, qf, cap, limit, full, p.scale_log2, lg,
                                   [&](int stage) {
                                     if (stage == 1 && more) load_keys(i + 1);
                                   });

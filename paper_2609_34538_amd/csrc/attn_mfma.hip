@@ -288,6 +288,12 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
     for (int dt = 0; dt < DT; ++dt) st.o[qt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
+  // fp32 at head dim 128 with two row tiles in one wave: the keys, the values and
+  // two chains of logits do not fit the registers together (one chain has 1.6
+  // times the rounding error), so the values are read after the logits; their
+  // part of the slot is refilled after the softmax.
+  constexpr bool kLateValues = sizeof(T) == 4 && DH == 128 && NQ == 2 && NW == 1;
+
   // Tile t's fragments from its ring slot into registers (keys; values as
   // V^T fragments, the draft block's token-major values gathered), and which
   // of its tokens each row sees.
@@ -298,9 +304,11 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
     for (int f = 0; f < 2 * KS; ++f)
       kf[f] = *reinterpret_cast<const u32x4 *>(slot + read_k[G::key_read_set(f)] + G::key_read_off(f));
     if (t < npt) {
+      if constexpr (!kLateValues) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        vf[dt] = *reinterpret_cast<const u32x4 *>(slot + (2 * KS + dt) * kFragBytes + 16 * lane);
+        for (int dt = 0; dt < DT; ++dt)
+          vf[dt] = *reinterpret_cast<const u32x4 *>(slot + (2 * KS + dt) * kFragBytes + 16 * lane);
+      }
       const int page = __builtin_amdgcn_readlane(page_id, t / TPP);
       const bool ok = page >= 0 && page < p.num_pages;
       limit = ok ? min(TT, S - pg0 * kPage - TT * t) : 0;
@@ -309,22 +317,40 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
         // Invisible tokens (past the prefix, or an unreadable page) enter P.V
         // with probability 0; their values are zeroed so that whatever the
         // cache holds there (NaN, Inf) contributes nothing.
-        const u32x4 keep = value_mask<T>(limit, lg);
+        if constexpr (!kLateValues) {
+          const u32x4 keep = value_mask<T>(limit, lg);
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) vf[dt] &= keep;
+          for (int dt = 0; dt < DT; ++dt) vf[dt] &= keep;
+        }
       }
 #pragma unroll
       for (int qt = 0; qt < NQ; ++qt) cap[qt] = 0x7fffffff;
     } else {
       // block values are token-major [TT][DH] in the slot: gather V^T
       const int u = t - npt;
+      if constexpr (!kLateValues) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-        vf[dt] = gather_block_values<T, DH>(slot + 2 * KS * kFragBytes, dt, ln, lg);
+        for (int dt = 0; dt < DT; ++dt)
+          vf[dt] = gather_block_values<T, DH>(slot + 2 * KS * kFragBytes, dt, ln, lg);
+      }
       limit = p.w - TT * u;
       full = false;
 #pragma unroll
       for (int qt = 0; qt < NQ; ++qt) cap[qt] = cap_blk[qt] - TT * u;
+    }
+  };
+
+  // kLateValues: the values of a tile whose first `limit` tokens are visible.
+  auto read_values = [&](int t, u32x4 (&vf)[DT], int limit) {
+    const uint8_t *slot = ring + (t % NB) * G::SLOT + 2 * KS * kFragBytes;
+    if (t < npt) {
+      const u32x4 keep = value_mask<T>(limit, lg);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+        vf[dt] = *reinterpret_cast<const u32x4 *>(slot + dt * kFragBytes + 16 * lane) & keep;
+    } else {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) vf[dt] = gather_block_values<T, DH>(slot, dt, ln, lg);
     }
   };
 
@@ -346,7 +372,14 @@ void attn_mfma_kernel(AttnParams p, int n_rg, int n_chunks) {
     const char *kbase = kl, *vbase = vl;
     if (refill && next < npt) tile_src(next, kbase, vbase);
     compute_tile<T, DH, NQ, true>(st, kf, vf, qf, cap, limit, full, p.scale_log2, lg, [&](int part) {
+      if constexpr (kLateValues) {
+        // lgkmcnt(0): the values are in registers before they are refilled
+        if (part == 2) __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4));
+      }
       if (refill) issue_part(next, part, kbase, vbase);
+      if constexpr (kLateValues) {
+        if (part == 1) read_values(t, vf, limit);
+      }
     });
   }
 

@@ -360,12 +360,11 @@ struct State {
 // LANE_SUM: st.l holds this lane's share of its row's sum (alpha is the same
 // in a row's 4 lanes), which the caller reduces over the 4 lanes when it
 // writes the row; otherwise st.l holds the row's sum after every tile.
-// TWO: on wherever its registers fit (two row tiles at head dim 128 spill in the
-// split grid). Error against 64 bits of one chain / two: 2 x 8 heads x 350-700
-// tokens x 28 rows, dh 96, 4.2e-7 / 2.7e-7; 8 heads x 4000 x 32 rows, dh 128,
-// 5.8e-7 / 3.1e-7 (15.6 / 15.8 us).
-template <typename T, int DH, int NQ, bool LANE_SUM = false,
-          bool TWO = sizeof(T) == 4 && (NQ == 1 || DH < 128), typename Hook>
+// fp32 logits run in two accumulation chains, which halves a chain's roundings.
+// Error against 64 bits of one chain / two: 2 x 8 heads x 350-700 tokens x 28
+// rows, dh 96, 4.2e-7 / 2.7e-7; 8 heads x 4000 x 32 rows, dh 128, 6.0e-7 / 5.0e-7,
+// with keys times 3 1.35e-6 / 7.9e-7 (the vector-ALU kernel: 6.3e-7, 1.21e-6).
+template <typename T, int DH, int NQ, bool LANE_SUM = false, typename Hook>
 __device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf)[DH / 16],
                                              const u32x4 (&vf)[DH / 16],
                                              const u32x4 (&qf)[NQ][Geo<T, DH, NQ, 1>::QK],
@@ -380,9 +379,11 @@ __device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf
   f32x4 sacc[NQ][E];
   hook(0);
   // reduction step outermost: the accumulators are independent, so no MFMA
-  // waits for the one before it. TWO: fp32 logits in two chains, which keeps
-  // that true with one row tile and halves a chain's roundings.
-  f32x4 odd[NQ];  // the second chain
+  // waits for the one before it. The two chains of fp32 keep that true with one
+  // row tile at a time, which is what the registers take at head dim 128.
+  constexpr bool F32 = sizeof(T) == 4;
+  constexpr int QG = F32 && DH == 128 ? 1 : NQ;  // row tiles side by side
+  f32x4 odd[NQ];                                 // the second chains
 #pragma unroll
   for (int qt = 0; qt < NQ; ++qt) {
     odd[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -390,25 +391,29 @@ __device__ __forceinline__ void compute_tile(State<DH, NQ> &st, const u32x4 (&kf
     for (int e = 0; e < E; ++e) sacc[qt][e] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 #pragma unroll
-  for (int ks = 0; ks < QK; ++ks) {
-    if constexpr (sizeof(T) == 2) {
+  for (int q0 = 0; q0 < NQ; q0 += QG) {
 #pragma unroll
-      for (int qt = 0; qt < NQ; ++qt)
+    for (int ks = 0; ks < QK; ++ks) {
+      if constexpr (!F32) {
 #pragma unroll
-        for (int e = 0; e < E; ++e)
-          sacc[qt][e] = mfma16x16x32(kf[e * QK + ks], qf[qt][ks], sacc[qt][e]);
-    } else {
+        for (int qt = 0; qt < NQ; ++qt)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+          for (int e = 0; e < E; ++e)
+            sacc[qt][e] = mfma16x16x32(kf[e * QK + ks], qf[qt][ks], sacc[qt][e]);
+      } else {
 #pragma unroll
-        for (int qt = 0; qt < NQ; ++qt) {
-          f32x4 &acc = TWO && (i & 1) ? odd[qt] : sacc[qt][0];
-          acc = mfma16x16x4(kf[ks][i], qf[qt][ks][i], acc);
-        }
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int qt = q0; qt < q0 + QG; ++qt) {
+            f32x4 &acc = i & 1 ? odd[qt] : sacc[qt][0];
+            acc = mfma16x16x4(kf[ks][i], qf[qt][ks][i], acc);
+          }
+      }
     }
+    if constexpr (QG < NQ) sacc[q0][0] += odd[q0];
   }
   hook(1);
-  if constexpr (TWO) {
+  if constexpr (F32 && QG == NQ) {
 #pragma unroll
     for (int qt = 0; qt < NQ; ++qt) sacc[qt][0] += odd[qt];
   }

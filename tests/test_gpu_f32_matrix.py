@@ -72,3 +72,27 @@ def test_invisible_positions_and_bad_pages():
     out = das.attn_policy(cache, bad, 0, 2, wl.depth_R, q, kb, vb)
     assert int(err.item()) & das.DEVERR_PAGE and torch.isfinite(out).all()
     assert torch.equal(out[:2], clean[:2])
+
+
+# one to four waves, every head dim, one and two row tiles in one wave
+PRECISION = [([4000, 2000], 8, 4, 128, 8, 8), ([4000, 2000], 8, 4, 128, 5, 4),
+             ([3000, 1500], 4, 2, 128, 16, 8), ([2000, 1000], 4, 4, 128, 16, 8),
+             ([2000, 1000], 4, 8, 128, 12, 8), ([3000, 1500], 8, 4, 96, 8, 8),
+             ([3000, 1500], 8, 4, 64, 5, 8), ([3000, 1500], 24, 1, 128, 16, 8)]
+
+
+@pytest.mark.parametrize("lens,hkv,group,dh,w,pps", PRECISION)
+def test_split_grid_no_less_precise_than_the_vector_kernel(lens, hkv, group, dh, w, pps):
+    """Keys three times the usual size: the logits' rounding dominates. Relative
+    2-norm error against 64 bits, matrix cores and vector ALU on the same inputs."""
+    wl, cd, cache, batch, q, kb, vb = _data(lens, hkv, group, dh, w)
+    cd.k_pool.mul_(3.0)
+    kb = kb * 3.0
+    ref, _ = oracle_call(cd, 0, 2, wl.depth_R, q, kb, vb, range(2))
+    ref = torch.as_tensor(ref, device=DEV)
+    err = {}
+    for path in ("auto", "valu"):
+        out = das.attn_policy(cache, batch, 0, 2, wl.depth_R, q, kb, vb, path=path,
+                              pages_per_split=pps)
+        err[path] = float((out.double() - ref).norm() / ref.norm())
+    assert err["auto"] <= err["valu"], err
