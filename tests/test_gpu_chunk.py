@@ -37,19 +37,26 @@ def _check(wl, cd, batch_args, what):
     assert_lse_close(lse, ref_lse, what + " lse")
 
 
+# (KV heads, group, head dim, block width) over EDGES
+FEW_TILES = [(1, 1, 64, 1), (3, 1, 96, 16), (2, 1, 128, 33), (3, 1, 64, 64), (1, 8, 96, 2),
+             (3, 5, 128, 13), (2, 8, 64, 15), (30, 1, 96, 7)]
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
-@pytest.mark.parametrize("hkv,group,dh,w", [
-    (1, 1, 64, 1), (3, 1, 96, 16), (2, 1, 128, 33), (3, 1, 64, 64), (1, 8, 96, 2), (3, 5, 128, 13),
-    (2, 8, 64, 15), (30, 1, 96, 7)])
+@pytest.mark.parametrize("hkv,group,dh,w", FEW_TILES)
 def test_few_tiles(dtype, hkv, group, dh, w):
     wl, cd, args = _data(EDGES, dtype, hkv, group, dh, w)
     _check(wl, cd, args, f"{dtype} hkv={hkv} G={group} dh={dh} w={w}")
 
 
+SEVERAL_CHUNKS = [([3000, 5, 0, 1111], 2, 1, 96, 9), ([9001], 1, 4, 128, 4),
+                  ([1200, 700], 3, 2, 64, 25), ([2500, 64], 3, 8, 128, 10),
+                  ([40000], 1, 1, 64, 1)]
+
+
+# the last shape: chunks in fp32, the shared ring in bf16
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
-@pytest.mark.parametrize("lens,hkv,group,dh,w", [
-    ([3000, 5, 0, 1111], 2, 1, 96, 9), ([9001], 1, 4, 128, 4), ([5000, 700], 3, 2, 64, 25),
-    ([2500, 64], 3, 8, 128, 10), ([40000], 1, 1, 64, 1)])
+@pytest.mark.parametrize("lens,hkv,group,dh,w", SEVERAL_CHUNKS + [([5000, 700], 3, 2, 64, 25)])
 def test_several_chunks(dtype, lens, hkv, group, dh, w):
     wl, cd, args = _data(lens, dtype, hkv, group, dh, w)
     _check(wl, cd, args, f"{dtype} lens={lens} hkv={hkv} G={group} dh={dh} w={w}")

@@ -16,9 +16,9 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
-@pytest.mark.parametrize("path", ["valu", "mfma", "balanced"])
+@pytest.mark.parametrize("path", ["valu", "mfma", "balanced", "auto"])  # auto: chunks
 def test_graph_replay_matches_eager(path):
-    pps = 0 if path == "balanced" else 2
+    pps = 0 if path in ("balanced", "auto") else 2
     wl = dg.scaled(dg.WORKLOADS[5], batch=5, hq=6, hkv=3, layers=2, prefix=(0, 400))
     torch.manual_seed(0)
     cd = dg.make_cache(wl, DEV, prefix_lens=[0, 65, 200, 333, 400])

@@ -227,13 +227,16 @@ def test_non_finite_cache_past_the_prefix_is_ignored(name, path):
     assert_close(out, ref, wl.dtype, f"{name} {path} with non-finite cache past the prefix")
 
 
-@pytest.mark.parametrize("lens,hkv,group,dh,w", [
-    ([4000, 64, 3999, 0, 1500], 11, 4, 96, 16), ([7000], 8, 8, 128, 32), ([6913], 8, 8, 64, 32),
-    ([300] * 3 + [0, 257], 50, 8, 64, 32)])
+EVEN_SPLITS = [([4000, 64, 3999, 0, 1500], 11, 4, 96, 16), ([7000], 8, 8, 128, 32),
+               ([6913], 8, 8, 64, 32), ([300] * 3 + [0, 257], 50, 8, 64, 32),
+               ([6000], 96, 1, 64, 33)]
+
+
+@pytest.mark.parametrize("lens,hkv,group,dh,w", EVEN_SPLITS)
 def test_even_splits_of_wide_blocks(lens, hkv, group, dh, w):
     """Blocks of more than 32 query rows whose library-chosen splits would
-    leave more than one round of workgroups take even splits: prefixes that
-    end inside, at the end of and before the last one."""
+    leave workgroups past a round take even splits: prefixes that end inside,
+    at the end of and before the last one."""
     wl = dg.scaled(W[3], batch=len(lens), hq=hkv * group, hkv=hkv, dh=dh, layers=1,
                    prefix=(0, max(lens)), draft_depths=(2,), draft_widths=(w,), verify_width=w,
                    paged_random=True)

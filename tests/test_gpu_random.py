@@ -60,8 +60,9 @@ def test_random_shapes(seed):
 
 @pytest.mark.parametrize("seed", range(1000, 1128))
 def test_random_shapes_fp32(seed):
-    """fp32 caches (vector-ALU kernel only) at every head dim and block width,
-    so every row-tile size of that kernel (4, 8, 16, 32 rows) is met."""
+    """fp32 caches at every head dim and block width: the library's choice (split
+    grid, chunks, vector ALU) and the vector-ALU kernel, so every row-tile size
+    of that kernel (4, 8, 16, 32 rows) is met."""
     wl, lens, pps, rng = _case(seed)
     wl = dg.scaled(wl, dtype=torch.float32)
     torch.manual_seed(seed)
@@ -72,10 +73,12 @@ def test_random_shapes_fp32(seed):
     w = wl.draft_widths[0]
     q, kb, vb = dg.block_inputs(cd, w, kappa, DEV)
     ref, ref_lse = oracle_call(cd, 1, kappa, nu, q, kb, vb, range(wl.batch))
-    lse = torch.empty((wl.batch, wl.hq, w), dtype=torch.float32, device=DEV)
-    out = das.attn_policy(cache, batch, 1, kappa, nu, q, kb, vb, lse=lse, pages_per_split=pps)
-    torch.cuda.synchronize()
-    what = (f"seed {seed} fp32: B={wl.batch} Hkv={wl.hkv} G={wl.group} dh={wl.dh} "
-            f"w={w} lens={lens} pps={pps} ({kappa},{nu})")
-    assert_close(out, ref, wl.dtype, what)
-    assert_lse_close(lse, ref_lse, what)
+    for path in ("auto", "valu"):
+        lse = torch.empty((wl.batch, wl.hq, w), dtype=torch.float32, device=DEV)
+        out = das.attn_policy(cache, batch, 1, kappa, nu, q, kb, vb, lse=lse, path=path,
+                              pages_per_split=pps)
+        torch.cuda.synchronize()
+        what = (f"seed {seed} fp32 {path}: B={wl.batch} Hkv={wl.hkv} G={wl.group} dh={wl.dh} "
+                f"w={w} lens={lens} pps={pps} ({kappa},{nu})")
+        assert_close(out, ref, wl.dtype, what)
+        assert_lse_close(lse, ref_lse, what)

@@ -1,7 +1,7 @@
 """Calls that run concurrently on separate streams, each with its own
 workspace, give the same bytes as the same calls run one after another: the
-balanced schedule and the split grid side by side, enqueued from one host
-thread and from two."""
+balanced schedule, the split grid and the workgroup-per-chunk kernel side by
+side, enqueued from one host thread and from one each."""
 
 from __future__ import annotations
 
@@ -25,13 +25,15 @@ def _setup():
     torch.manual_seed(11)
     cd = dg.make_cache(wl, DEV, prefix_lens=[2999, 0, 700, 1500, 64, 2048])
     cache, batch = wrap(cd)
-    # the same cache seen as a single sequence (the split grid)
+    # the same cache seen as a single sequence: the split grid, or chunks where
+    # the library chooses
     _, single = wrap(cd, table=cd.block_table[:1], prefix_lens=cd.prefix_lens[:1])
     q, kb, vb = dg.block_inputs(cd, 8, 2, DEV)
     calls = {
         "balanced": (batch, q, kb, vb, "balanced"),
         "split": (single, q[:1].contiguous(), kb[:1].contiguous(), vb[:1].contiguous(), "mfma"),
     }
+    calls["chunks"] = calls["split"][:4] + ("auto",)
     return wl, cache, calls
 
 

@@ -7,6 +7,9 @@ import random
 
 import pytest
 
+import test_gpu_chunk as chunk
+import test_gpu_f32_matrix as f32
+import test_gpu_parity as parity
 from host_plan import plan
 
 
@@ -101,3 +104,37 @@ def test_any_workspace_that_was_enough_stays_enough():
             assert plan(dtype, b, hkv, g, dh, pages, w, workspace=valu.workspace).status == 0
             fits = fits or valu.workspace <= 64 << 20
         assert (plan(dtype, b, hkv, g, dh, pages, w, noalloc=True).status == 0) == fits
+
+
+def _pages(lens, w):
+    """Columns of the block table that the GPU tests' caches have."""
+    return max(max(1, -(-(s + w) // 64)) for s in lens)
+
+
+@pytest.mark.parametrize("shapes,kernel", [(f32.CHUNK, "chunk"), (f32.BALANCED, "balanced"),
+                                           (f32.SPLIT, "split"), (f32.PRECISION, "split")],
+                         ids=["chunk", "balanced", "split", "precision"])
+def test_gpu_tests_run_the_kernels_they_name(shapes, kernel):
+    for lens, hkv, g, dh, w, pps in shapes:
+        p = plan("f32", len(lens), hkv, g, dh, _pages(lens, w), w, pps=pps)
+        assert p.kernel == kernel, (lens, hkv, g, dh, w, p)
+
+
+def test_gpu_tests_of_smaller_workspaces_and_chunks():
+    for hkv, lens, dh, w, kernel, fallback in f32.SMALLER_WORKSPACE:
+        at = ("f32", len(lens), hkv, 1, dh, _pages(lens, w), w)
+        valu = plan(*at, path="valu")
+        assert plan(*at).kernel == kernel
+        assert plan(*at, workspace=valu.workspace).kernel == fallback
+        # what the library asks for holds the vector-ALU plan as well or not
+        assert valu.status == 0
+    for dtype in ("bf16", "f32"):
+        for hkv, g, dh, w in chunk.FEW_TILES:
+            n, pages = len(chunk.EDGES), _pages(chunk.EDGES, w)
+            assert plan(dtype, n, hkv, g, dh, pages, w).kernel == "chunk"
+        for lens, hkv, g, dh, w in chunk.SEVERAL_CHUNKS:
+            p = plan(dtype, len(lens), hkv, g, dh, _pages(lens, w), w)
+            assert p.kernel == "chunk" and p.nsplit > 1, (dtype, lens, hkv, g, dh, w, p)
+    for lens, hkv, g, dh, w in parity.EVEN_SPLITS:
+        p = plan("bf16", len(lens), hkv, g, dh, _pages(lens, w), w)
+        assert p.kernel == "split" and p.nsplit > 1, (lens, hkv, g, dh, w, p)

@@ -25,7 +25,8 @@ def _inputs(wl, lens, w, d):
 
 
 @pytest.mark.parametrize("dtype,path", [(torch.bfloat16, "mfma"), (torch.bfloat16, "valu"),
-                                        (torch.bfloat16, "balanced"), (torch.float32, "valu")])
+                                        (torch.bfloat16, "balanced"), (torch.float32, "valu"),
+                                        (torch.bfloat16, "auto"), (torch.float32, "auto")])
 def test_noalloc_matches_policy_on_two_calls(dtype, path):
     big = dg.scaled(dg.WORKLOADS[5], dtype=dtype, batch=5, hq=8, hkv=4, layers=2,
                     prefix=(0, 0), draft_widths=(16,), verify_width=16)
