@@ -245,15 +245,18 @@ das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_at
 // every head dim, 1-512 rows):
 // - one chunk per unit needs no merge (3.9 us and the record traffic), but a
 //   CU takes no more than about 38 GB/s from a large pool in memory (50 of a
-//   batch's table width, which its lengths do not fill), so long units need several; with k > 1 a
-//   wave waits for every tile in turn (1 us and its arithmetic). The estimate
-//   below, in us per call and without the launch, weighs these, the whole
-//   stream (8.5 TB/s of the table's width: memory gives 6.3, a batch's lengths
-//   average less than its table, and between plans that are all bound by it the
-//   others decide) and the dispatch of many workgroups. Its constants are fitted
-//   to every cut of 3186 calls (8-256 units x 160-16000 tokens, every head dim, 8
-//   and 32 rows, one sequence and four ragged ones, pages spread over 48 GB and
-//   cached): the cut it takes is 1.3-1.4 % off the best one on average, and
+//   batch's table width, which its lengths do not fill), so long units need
+//   several; with k > 1 a wave waits for every tile in turn (1 us and its
+//   arithmetic; 0.5 us where the call is under 1 MB, which a loop reads from the
+//   L2: 4 fp32 heads x 256 tokens x 4 rows, dh 64, called eagerly 6.6 us with one
+//   chunk of five tiles per wave, 7.5 with five chunks and the merge's launch). The
+//   estimate below, in us per call and without the launch, weighs these, the
+//   whole stream (8.5 TB/s of the table's width: memory gives 6.3, a batch's
+//   lengths average less than its table, and between plans that are all bound by
+//   it the others decide) and the dispatch of many workgroups. Its constants are
+//   fitted to every cut of 3186 calls (8-256 units x 160-16000 tokens, every head
+//   dim, 8 and 32 rows, one sequence and four ragged ones, pages spread over 48 GB
+//   and cached): the cut it takes is 1.3-1.4 % off the best one on average, and
 //   against the split grid in its first form 0.92 at worst (46 calls below 0.97).
 //   Single short sequence (55 heads, 331 tokens): 8.9 -> 6.8 us; 4 x 55 heads x
 //   512-2048: 33.5 -> 19.4.
@@ -303,10 +306,11 @@ void plan_chunks(const das_cache *c, const das_batch *b, int w, size_t ws_bytes,
   const float t_cmp = nq * c->head_dim * (es == 4 ? 16.f / 2400.f : 0.002f);
   const float t_hbm = static_cast<float>(seq_heads) * tiles * tile_bytes / 8.5e6f;
   const float t_wg = nq == 2 ? 0.0115f : 0.0065f;
+  const float t_tile = seq_heads * tiles * tile_bytes < 1e6f ? 0.5f : 1.f;
   const size_t stride = piece_record_bytes(plan->rows, c->head_dim, es);
   auto time = [&](int k, int ns) {
     const int m = (units * ns + kNumCUs - 1) / kNumCUs;
-    float t = k * (1.f + t_cmp);
+    float t = k * (t_tile + t_cmp);
     if (m * k * t_cmp > t) t = m * k * t_cmp;
     if (m * k * t_mem > t) t = m * k * t_mem;
     if (n_rt > 1) t *= 1.1f;

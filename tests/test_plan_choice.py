@@ -88,6 +88,12 @@ def test_chunks_against_the_split_grid(hkv, dh, pages, w, kernel, nsplit):
     assert (p.kernel, p.nsplit) == (kernel, nsplit), p
 
 
+def test_calls_under_a_megabyte_take_one_launch():
+    """4 heads x 256 tokens in fp32 (0.5 MB): five tiles per wave in one chunk."""
+    p = plan("f32", 1, 4, 1, 64, 4, 4)
+    assert (p.kernel, p.nsplit, p.merge) == ("chunk", 1, False), p
+
+
 def test_any_workspace_that_was_enough_stays_enough():
     """A call's own workspace size is accepted; fp32 calls also run in the
     vector-ALU plan's, and in the library's scratch wherever either fits."""
