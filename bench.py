@@ -55,9 +55,10 @@ TRAFFIC_SOURCES = ["paper_2609_34538_amd/csrc/attn_mfma.hip",
                    "paper_2609_34538_amd/csrc/mfma_tile.h",
                    "paper_2609_34538_amd/csrc/das_api.hip",
                    "paper_2609_34538_amd/csrc/das_internal.h"]
-MEASURED_TRAFFIC = {("das-wave-step-bf16", "33679d349612bf4f"): 4_467_675_320,
-                    ("long-prefix-gqa-bf16", "33679d349612bf4f"): 310_268_609,
-                    ("ragged-paged-bf16", "33679d349612bf4f"): 834_102_880}
+MEASURED_TRAFFIC = {("das-wave-step-bf16", "cb816db5e57d0df8"): 4_468_009_913,
+                    ("long-prefix-gqa-bf16", "cb816db5e57d0df8"): 310_302_139,
+                    ("ragged-paged-bf16", "cb816db5e57d0df8"): 834_120_913,
+                    ("single-seq-looped-bf16", "cb816db5e57d0df8"): 47_018_528}
 
 
 def kernel_digest():

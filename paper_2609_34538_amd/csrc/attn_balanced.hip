@@ -1,5 +1,6 @@
 // Balanced persistent matrix-core attention for batches of sequences with
-// different prefix lengths (Eq. (2)-(3) over a ragged batch).
+// different prefix lengths (Eq. (2)-(3) over a ragged batch), bf16 and fp32 (in
+// 16-token tiles, four to a page; tile counts below are bf16's).
 //
 // Work layout. A unit is one (sequence b, KV head) pair: its query block
 // (w * G <= 32 rows) against the sequence's prefix and the draft block. A
@@ -23,9 +24,9 @@
 // the same box. At the end
 // of a unit (or of its range) the worker writes the unit's normalised output
 // when it processed the whole unit, otherwise a piece (the running maximum
-// m, the sum l and the normalised output O / l in fp16 under a per-row
-// power-of-two scale) that the merge kernel combines with the unit's other
-// pieces. Only the range's first unit can end as a piece in the middle of
+// m, the sum l and the output: for bf16 O / l in fp16 under a per-row
+// power-of-two scale, for fp32 O in fp32) that the merge kernel combines with the
+// unit's other pieces. Only the range's first unit can end as a piece in the middle of
 // the range; its record waits in LDS and is written with the range's last
 // flush, because writes in the middle of the stream delay the reads at the
 // DRAM (width-32 calls 0.768 -> 0.788 and 0.771 -> 0.805 of 8 TB/s, ragged

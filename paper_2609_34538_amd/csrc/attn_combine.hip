@@ -81,7 +81,7 @@ __global__ __launch_bounds__(64) void attn_combine_kernel(AttnParams p, int skip
       n3 += sc * ov[k].w;
     }
   }
-  // splits beyond the first 16, merged in the same online form
+  // splits beyond the first kEager, merged in the same online form
   for (int s0 = kEager; s0 < ns && live; ++s0) {
     const float m = p.ws_m[mbase + s0], l = p.ws_l[mbase + s0];
     const float4 o = *reinterpret_cast<const float4 *>(p.ws_o + (obase + static_cast<size_t>(s0) * p.rows) * DH + c);

@@ -1,4 +1,6 @@
-// Matrix-core (MFMA) policy-attention kernel for bf16 caches (Eq. (2)-(3)).
+// Matrix-core (MFMA) policy-attention kernel over prefix splits (Eq. (2)-(3)),
+// for bf16 caches and, in 16-token tiles, fp32 ones (mfma_tile.h). Tile sizes
+// and fragment layouts below are those of bf16.
 //
 // One wave per chunk = (sequence, KV head, row tile of 16 * NQ query rows,
 // prefix split of up to pages_per_split pages). Blocks of up to 32 query rows
@@ -15,11 +17,11 @@
 // XCD, where they share its L2.
 //
 // A chunk fetches its sequence's prefix length, its page ids and its Q rows
-// (into registers) in one memory round trip, then streams its 32-token tiles (two per prefix
-// page, then the draft block's) through a ring of NB LDS slots filled by the
-// direct-to-LDS loads of gfx950 (buffer_load_dwordx4 ... lds for prefix
-// pages, global_load_lds_dwordx4 for the draft block), NB tiles ahead of the
-// tile being computed; the loads of the next tile are spread over the
+// (into registers) in one memory round trip, then streams its tiles (two per
+// prefix page in bf16, four in fp32, then the draft block's) through a ring of
+// NB LDS slots filled by the direct-to-LDS loads of gfx950 (buffer_load_dwordx4
+// ... lds for prefix pages, global_load_lds_dwordx4 for the draft block), NB
+// tiles ahead of the tile being computed; the loads of the next tile are spread over the
 // computation of the current one. The wave waits on its own vector-memory
 // counter for the data it reads. A prefix tile's loads address a buffer
 // resource per tile with per-lane offsets and a uniform part in an SGPR; each
@@ -44,11 +46,11 @@
 // a 32-token tile of that page is one contiguous block. The draft block's
 // values are token-major; their V^T fragments are gathered from LDS.
 //
-// A chunk ends by writing its piece record (m, l and O / l in fp16 under a
-// per-row power-of-two scale) to the workspace for the combine kernel, or,
-// when its sequence has a single split, the normalised output. Query rows of a row tile: row = i * G + g (block position i,
-// head kvh * G + g). Logits are scaled into base-2 units after the product,
-// inside the exponent's fused multiply-add.
+// A chunk ends by writing its piece record (write_piece_row: fp16 outputs for
+// bf16, fp32 for fp32) to the workspace for the combine kernel, or, when its
+// sequence has a single split, the normalised output. Query rows of a row tile:
+// row = i * G + g (block position i, head kvh * G + g). Logits are scaled into
+// base-2 units after the product, inside the exponent's fused multiply-add.
 
 #include "mfma_tile.h"
 

@@ -1,7 +1,7 @@
 // Vector-ALU policy-attention kernel (Eq. (2)-(3)) over one prefix split.
 //
-// The only path for fp32 caches, and a bf16 path for comparison with the
-// matrix-core kernel. One workgroup of four waves = (prefix split, KV head,
+// DAS_PATH_VALU, for comparison with the matrix-core kernels, and fp32 calls
+// whose workspace holds this kernel's partials but not theirs. One workgroup of four waves = (prefix split, KV head,
 // sequence x row tile of RT query rows, RT = 4, 8, 16 or 32 chosen from the
 // block's rows). The split's tiles (the draft block first on split 0, then
 // its prefix pages) pass through LDS as fp32: keys token-major and values

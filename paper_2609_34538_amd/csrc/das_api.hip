@@ -99,13 +99,13 @@ struct Plan {
 
 // Prefix pages of one sequence are cut into splits of pages_per_split pages;
 // each (split, KV head, row tile) is one chunk of work, one workgroup. The
-// default aims for at least ~1024 chunks (four single-wave workgroups per
-// compute unit of a 256-CU part): with `units` = sequences x KV heads x row
-// tiles, each (sequence, KV head) gets max(2, the largest power of two
-// <= 1024 / units) splits, and a split holds between 2 and 32 pages.
-// (Measured on MI355X over 1-64 pages per split on the single-sequence,
-// ragged, long-prefix and wave-step workloads: this picks the best split
-// size on three and one within 0.5 % of the best on the fourth.)
+// default aims for about 512 chunks (two single-wave workgroups per compute
+// unit of a 256-CU part; 2048 row tiles where they share a workgroup): with
+// `units` = sequences x KV heads x row tiles, each (sequence, KV head) gets
+// max(2, the largest power of two <= 512 / units) splits, and a split holds
+// between 2 and 32 pages. (Single-sequence call 16.2 / 15.8 / 15.4 / 16.0 /
+// 17.0 / 19.8 us at 2 / 3 / 4 / 5 / 6 / 8 pages, the default 4; four such
+// sequences 39.7 against 40.5 with a target of 1024.)
 das_status plan_path(const das_cache *c, const das_batch *b, int w, const das_attn_options *o,
                      int path, Plan *plan) {
   const int es = elem_bytes(c->dtype);

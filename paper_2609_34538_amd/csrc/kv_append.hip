@@ -14,8 +14,11 @@
 //    fit (a full group is one 16-byte store for bf16). The run of a group is
 //    the same in every lane, so the choice of stores is a scalar branch, and no
 //    group is written in two pieces.
-// Commits of few tokens are bound by the dispatch of the waves and their round
-// trips, wide ones by memory. Against staging 16 tokens from the first new
+// Commits of few tokens are bound by the dispatch of the waves and their three
+// dependent round trips, and by partial lines where they begin or end inside a
+// group: 8 tokens that fill their groups 9.2 us, 7 tokens from position 187, in
+// two groups, 12.6 (32 + 32 planes x 4 layers x 55 heads, one buffer, graph
+// replays). Wide ones are bound by memory. Against staging 16 tokens from the first new
 // position with workgroup barriers and per-lane runs: 32 + 32 planes x 4 layers
 // x 55 heads x 1, 7, 30 and 64 tokens 10.6, 14.8, 45.4, 80.6 -> 9.6, 14.7,
 // 41.8, 70.5 us (265 MB, 3.8 TB/s). Measured and not kept: two or four units
